@@ -63,7 +63,8 @@ PT_M, PT_TMIN, PT_TMAX = 32, 0.2, 2.0
 DSEED = 20110856
 F_TOL = 0.5
 KERNEL_SOURCES = [os.path.join(ROOT, "paper_2011_08560_amd", "csrc", f)
-                  for f in ("sweep.hip", "kernels.hpp", "philox.hpp", "nfm_internal.hpp")]
+                  for f in ("sweep_wave.hpp", "sweep_size.hip", "sweep_queue.hip", "sweep.hip", "kernels.hpp", "philox.hpp",
+                            "nfm_internal.hpp")]
 
 
 def kernel_source_digest() -> str:

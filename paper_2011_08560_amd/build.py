@@ -15,8 +15,11 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "libnfm.so")
 BUILD = os.path.join(HERE, "_build")
-SOURCES = ["api.cpp", "mlp_api.cpp", "stats.cpp", "lattice.hip", "tables.hip", "sweep.hip", "recursion.hip", "wl.hip", "features.hip",
-           "mlp.hip"]
+# (source, object, definitions): the sweep kernels compile per lattice size and per queue form
+SOURCES = ([("sweep_queue.hip", f"sweep_queue{q}", [f"-DNFM_SPEC={q}"]) for q in (0, 1)]
+           + [("sweep_size.hip", f"sweep_size{L}", [f"-DNFM_SIZE={L}"]) for L in (12, 10, 8, 6, 4, 2)]
+           + [(f, f.split(".")[0], []) for f in ("api.cpp", "mlp_api.cpp", "stats.cpp", "lattice.hip", "tables.hip",
+                                                 "sweep.hip", "recursion.hip", "wl.hip", "features.hip", "mlp.hip")])
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["-O3", "-std=c++17", "-fPIC", "--offload-arch=gfx950", "-ffp-contract=off",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
@@ -33,13 +36,14 @@ SANITIZE = ["-Xarch_host", "-fsanitize=address", "-Xarch_host", "-fsanitize=unde
             "-Xarch_host", "-fno-sanitize-recover=undefined", "-Xarch_host", "-fno-omit-frame-pointer"]
 
 
-def _compile(src: str, sanitize: bool = False) -> str:
-    obj = os.path.join(BUILD, os.path.basename(src) + (".san.o" if sanitize else ".o"))
+def _compile(unit, sanitize: bool = False) -> str:
+    src, name, defs = unit
+    obj = os.path.join(BUILD, name + (".san.o" if sanitize else ".o"))
     lang = ["-x", "hip"]
-    cmd = [HIPCC, *lang, *FLAGS, *(SANITIZE if sanitize else []), "-c", os.path.join(CSRC, src), "-o", obj]
+    cmd = [HIPCC, *lang, *FLAGS, *defs, *(SANITIZE if sanitize else []), "-c", os.path.join(CSRC, src), "-o", obj]
     res = subprocess.run(cmd, capture_output=True, text=True)
     if res.returncode != 0:
-        raise RuntimeError(f"hipcc failed for {src}:\n{res.stderr[-4000:]}")
+        raise RuntimeError(f"hipcc failed for {name}:\n{res.stderr[-4000:]}")
     return obj
 
 
@@ -49,8 +53,8 @@ def build(verbose: bool = True, sanitize: bool = False) -> str:
     e.g. LD_PRELOAD=$(hipcc -print-file-name=libclang_rt.asan-x86_64.so) ASAN_OPTIONS=detect_leaks=0);
     build again without it afterwards."""
     os.makedirs(BUILD, exist_ok=True)
-    with cf.ThreadPoolExecutor(max_workers=len(SOURCES)) as ex:
-        objs = list(ex.map(lambda src: _compile(src, sanitize), SOURCES))
+    with cf.ThreadPoolExecutor(max_workers=min(len(SOURCES), os.cpu_count() or 8)) as ex:
+        objs = list(ex.map(lambda unit: _compile(unit, sanitize), SOURCES))
     tmp = OUT + ".tmp"
     # -z defs: an undefined symbol is a link error here, not a load error on the GPU host (the
     # sanitized build takes the sanitizer runtimes from the preloading process instead)

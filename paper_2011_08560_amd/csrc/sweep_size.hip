@@ -1,0 +1,108 @@
+// Sweep kernels of one lattice size, L = NFM_SIZE (one compilation per size, in parallel).
+#include <algorithm>
+
+#include "sweep_launch.hpp"
+#include "sweep_wave.hpp"
+
+namespace nfm {
+
+template <int L, bool SPEC>
+__global__ void __launch_bounds__(128) k_sweeps_ws(SweepArgs A) {
+  extern __shared__ uint32_t stab[];  // addressed from LDS address 0
+  (void)stab;
+  // the role is uniform per wave: a scalar branch, so that each wave meets only its own barriers
+  const int role = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  if (role == 0) {
+    // the sampling wave's decisions form the critical chain: its instructions go first
+    __builtin_amdgcn_s_setprio(3);
+    sweep_wave<L, SPEC, false, true, true>(A, (int)blockIdx.x);
+  } else {
+    generate_words<L>(A, (int)blockIdx.x);
+  }
+}
+
+template <int L, bool SPEC, bool PT, bool XT>
+__global__ void __launch_bounds__(64) k_sweeps(SweepArgs A) {
+  extern __shared__ uint32_t stab[];  // addressed from LDS address 0 by sweep_wave
+  (void)stab;
+  // scalar uniform rounds for the compact and tempering forms (usually several waves per SIMD),
+  // except the L = 6 tempering form, where they cost a resident wave (139 against 125 VGPRs)
+  sweep_wave<L, SPEC, PT, XT, false, !XT && !(PT && L == 6)>(A, (int)blockIdx.x);
+}
+
+template <int L, bool SPEC, bool PT, bool XT = false>
+static hipError_t launch_LS(const SweepArgs& a, int n_waves, size_t lds_bytes, hipStream_t s) {
+  // The kernel addresses its dynamic LDS block from address 0, which is only valid
+  // when the compiler placed nothing else in LDS.
+  static int checked = 0;
+  if (!checked) {
+    hipFuncAttributes attr;
+    hipError_t e = hipFuncGetAttributes(&attr, reinterpret_cast<const void*>(&k_sweeps<L, SPEC, PT, XT>));
+    if (e != hipSuccess) return e;
+    if (attr.sharedSizeBytes != 0) return hipErrorInvalidKernelFile;
+    checked = 1;
+  }
+  note_kernel(PT ? "k_sweeps_pt" : SPEC ? "k_sweeps_spec" : XT ? "k_sweeps_xt" : "k_sweeps", L);
+  hipLaunchKernelGGL((k_sweeps<L, SPEC, PT, XT>), dim3(n_waves), dim3(64), lds_bytes, s, a);
+  return hipGetLastError();
+}
+
+template <int L, bool SPEC>
+static hipError_t launch_ws(const SweepArgs& a, int n_waves, size_t lds_bytes, hipStream_t s) {
+  static int checked = 0;
+  if (!checked) {
+    hipFuncAttributes attr;
+    hipError_t e = hipFuncGetAttributes(&attr, reinterpret_cast<const void*>(&k_sweeps_ws<L, SPEC>));
+    if (e != hipSuccess) return e;
+    if (attr.sharedSizeBytes != 0) return hipErrorInvalidKernelFile;
+    checked = 1;
+  }
+  note_kernel(SPEC ? "k_sweeps_ws_spec" : "k_sweeps_ws", L);
+  hipLaunchKernelGGL((k_sweeps_ws<L, SPEC>), dim3(n_waves), dim3(128), lds_bytes, s, a);
+  return hipGetLastError();
+}
+
+template <int L>
+hipError_t launch_L(SweepArgs a, int n_waves, int lds_rows, int hist_levels, int n_cu, int hist_mode,
+                           int ws_mode, bool spec, bool pt, hipStream_t s) {
+  const size_t jb = (size_t)jk_words(L) * 4;
+  if (pt) return launch_LS<L, false, true>(a, n_waves, (size_t)a.pt_M * 32 + 3 * 256 + jb, s);
+  const void* f = spec ? reinterpret_cast<const void*>(&k_sweeps<L, true, false, false>)
+                       : reinterpret_cast<const void*>(&k_sweeps<L, false, false, false>);
+  const int want = (n_waves + n_cu - 1) / std::max(n_cu, 1);
+  const HistPlan h = plan_hist(f, (size_t)lds_rows * 32 + jb, lds_rows, hist_levels, want, hist_mode);   // table, couplings
+  if (hist_mode == 0) {
+    // the expanded table (and every level of the histogram) when it costs no resident workgroups
+    const void* fx = reinterpret_cast<const void*>(&k_sweeps<L, false, false, true>);
+    const size_t lds_x = (size_t)hist_levels * 32 + jb + (size_t)hist_levels * 4;
+    int occ_x = 0, occ = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ_x, fx, 64, lds_x) == hipSuccess &&
+        hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, f, 64, h.lds) == hipSuccess && occ_x >= std::min(occ, want)) {
+      if (ws_mode != 1) {
+        const size_t lds_w = (size_t)ws_ring_base(hist_levels, jk_words(L), hist_levels) + 3 * (size_t)ws_slot_bytes<L>();
+        const void* fw = spec ? reinterpret_cast<const void*>(&k_sweeps_ws<L, true>)
+                              : reinterpret_cast<const void*>(&k_sweeps_ws<L, false>);
+        int occ_w = 0;
+        const bool fits = hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ_w, fw, 128, lds_w) == hipSuccess &&
+                          occ_w >= want;
+        if (ws_mode == 2 ? occ_w >= 1 : (fits && n_waves <= 4 * n_cu)) {
+          a.hist_margin = hist_levels;
+          a.hist_n = hist_levels;
+          return spec ? launch_ws<L, true>(a, n_waves, lds_w, s) : launch_ws<L, false>(a, n_waves, lds_w, s);
+        }
+      }
+      if (!spec) {
+        a.hist_margin = hist_levels;
+        a.hist_n = hist_levels;
+        return launch_LS<L, false, false, true>(a, n_waves, lds_x, s);
+      }
+    }
+  }
+  a.hist_margin = h.margin;
+  a.hist_n = h.n;
+  return spec ? launch_LS<L, true, false>(a, n_waves, h.lds, s) : launch_LS<L, false, false>(a, n_waves, h.lds, s);
+}
+
+template hipError_t launch_L<NFM_SIZE>(SweepArgs, int, int, int, int, int, int, bool, bool, hipStream_t);
+
+}  // namespace nfm
