@@ -20,6 +20,10 @@ __global__ void __launch_bounds__(64, MAXL <= 8 ? 3 : MAXL <= 10 ? 2 : 1) k_swee
   extern __shared__ uint32_t stab[];
   (void)stab;
   if constexpr (SOLO) asm volatile("" ::: "a255");
+  // A wave alone on its SIMD takes the uniform rounds staged (L = 12: 89.5 us per sweep against 93.6
+  // on the scalar unit); beside others, and where speculation's second reads need the registers, on
+  // the scalar unit.
+  constexpr Gen gen = SOLO && !SPEC ? kGenStaged : kGenScalar;
   for (;;) {
     __syncthreads();  // the previous item's table reads are done before the next table is loaded
     int item = 0;
@@ -30,12 +34,12 @@ __global__ void __launch_bounds__(64, MAXL <= 8 ? 3 : MAXL <= 10 ? 2 : 1) k_swee
     if (item >= n_items) break;
     const int wave = order[item];
     switch (A.reals[A.wave_real[wave]].L) {
-      case 2: sweep_wave<2, SPEC, false, false, false, true, true>(A, wave); break;
-      case 4: if constexpr (MAXL >= 4) sweep_wave<4, SPEC, false, false, false, true, true>(A, wave); break;
-      case 6: if constexpr (MAXL >= 6) sweep_wave<6, SPEC, false, false, false, true, true>(A, wave); break;
-      case 8: if constexpr (MAXL >= 8) sweep_wave<8, SPEC, false, false, false, true, true>(A, wave); break;
-      case 10: if constexpr (MAXL >= 10) sweep_wave<10, SPEC, false, false, false, true, true>(A, wave); break;
-      case 12: if constexpr (MAXL >= 12) sweep_wave<12, SPEC, false, false, false, true, true>(A, wave); break;
+      case 2: sweep_wave<2, SPEC, false, false, gen, true>(A, wave); break;
+      case 4: if constexpr (MAXL >= 4) sweep_wave<4, SPEC, false, false, gen, true>(A, wave); break;
+      case 6: if constexpr (MAXL >= 6) sweep_wave<6, SPEC, false, false, gen, true>(A, wave); break;
+      case 8: if constexpr (MAXL >= 8) sweep_wave<8, SPEC, false, false, gen, true>(A, wave); break;
+      case 10: if constexpr (MAXL >= 10) sweep_wave<10, SPEC, false, false, gen, true>(A, wave); break;
+      case 12: if constexpr (MAXL >= 12) sweep_wave<12, SPEC, false, false, gen, true>(A, wave); break;
       default: break;
     }
   }

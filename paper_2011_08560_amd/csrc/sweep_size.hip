@@ -6,7 +6,12 @@
 
 namespace nfm {
 
-template <int L, bool SPEC>
+// The sampling wave beside a generator wave. Its step is bound by the chain from one threshold read
+// to the next (115-125 cycles at every size with one read per attempt), so it reads the thresholds
+// of both outcomes ahead (the paired form), speculation asked for or not: 95 (L = 12) to 107 cycles
+// per step where each wave has a SIMD. With a pair of waves per SIMD the vector issue of both binds:
+// 116 at L = 4, 125 at L = 6.
+template <int L>
 __global__ void __launch_bounds__(128) k_sweeps_ws(SweepArgs A) {
   extern __shared__ uint32_t stab[];  // addressed from LDS address 0
   (void)stab;
@@ -15,19 +20,31 @@ __global__ void __launch_bounds__(128) k_sweeps_ws(SweepArgs A) {
   if (role == 0) {
     // the sampling wave's decisions form the critical chain: its instructions go first
     __builtin_amdgcn_s_setprio(3);
-    sweep_wave<L, SPEC, false, true, true>(A, (int)blockIdx.x);
+    sweep_wave<L, false, false, true, kGenWave>(A, (int)blockIdx.x);
   } else {
     generate_words<L>(A, (int)blockIdx.x);
   }
+}
+
+// The uniform rounds of a form: on the scalar unit for the compact and tempering forms (usually
+// several waves per SIMD, which leave it idle), except L = 6 tempering (unrolled planes, scalar
+// registers short). The expanded table usually means a wave alone on its SIMD: on the vector unit
+// (L = 8: 125 cycles per step against 130 staged), but staged at L = 12, where the sweep's start is
+// a small part of it (118 against 124); so is the compact form there, whose tables leave the SIMDs
+// one wave each (127 cycles against 136 on the scalar unit).
+template <int L, bool SPEC, bool PT, bool XT>
+constexpr Gen gen_of() {
+  if (XT) return L >= 12 ? kGenStaged : kGenVector;
+  if (L >= 12 && !SPEC && !PT) return kGenStaged;
+  return PT && L == 6 ? kGenVector : kGenScalar;
 }
 
 template <int L, bool SPEC, bool PT, bool XT>
 __global__ void __launch_bounds__(64) k_sweeps(SweepArgs A) {
   extern __shared__ uint32_t stab[];  // addressed from LDS address 0 by sweep_wave
   (void)stab;
-  // scalar uniform rounds for the compact and tempering forms (usually several waves per SIMD),
-  // except the L = 6 tempering form, where they cost a resident wave (139 against 125 VGPRs)
-  sweep_wave<L, SPEC, PT, XT, false, !XT && !(PT && L == 6)>(A, (int)blockIdx.x);
+  constexpr Gen gen = gen_of<L, SPEC, PT, XT>();
+  sweep_wave<L, SPEC, PT, XT, gen>(A, (int)blockIdx.x);
 }
 
 template <int L, bool SPEC, bool PT, bool XT = false>
@@ -47,18 +64,18 @@ static hipError_t launch_LS(const SweepArgs& a, int n_waves, size_t lds_bytes, h
   return hipGetLastError();
 }
 
-template <int L, bool SPEC>
-static hipError_t launch_ws(const SweepArgs& a, int n_waves, size_t lds_bytes, hipStream_t s) {
+template <int L>
+static hipError_t launch_ws(const SweepArgs& a, int n_waves, size_t lds_bytes, bool spec, hipStream_t s) {
   static int checked = 0;
   if (!checked) {
     hipFuncAttributes attr;
-    hipError_t e = hipFuncGetAttributes(&attr, reinterpret_cast<const void*>(&k_sweeps_ws<L, SPEC>));
+    hipError_t e = hipFuncGetAttributes(&attr, reinterpret_cast<const void*>(&k_sweeps_ws<L>));
     if (e != hipSuccess) return e;
     if (attr.sharedSizeBytes != 0) return hipErrorInvalidKernelFile;
     checked = 1;
   }
-  note_kernel(SPEC ? "k_sweeps_ws_spec" : "k_sweeps_ws", L);
-  hipLaunchKernelGGL((k_sweeps_ws<L, SPEC>), dim3(n_waves), dim3(128), lds_bytes, s, a);
+  note_kernel(spec ? "k_sweeps_ws_spec" : "k_sweeps_ws", L);
+  hipLaunchKernelGGL((k_sweeps_ws<L>), dim3(n_waves), dim3(128), lds_bytes, s, a);
   return hipGetLastError();
 }
 
@@ -70,25 +87,25 @@ hipError_t launch_L(SweepArgs a, int n_waves, int lds_rows, int hist_levels, int
   const void* f = spec ? reinterpret_cast<const void*>(&k_sweeps<L, true, false, false>)
                        : reinterpret_cast<const void*>(&k_sweeps<L, false, false, false>);
   const int want = (n_waves + n_cu - 1) / std::max(n_cu, 1);
-  const HistPlan h = plan_hist(f, (size_t)lds_rows * 32 + jb, lds_rows, hist_levels, want, hist_mode);   // table, couplings
+  const size_t staged = L >= 12 ? staged_bytes<L>() + 12 : 0;   // after the histogram, 16-byte aligned
+  const HistPlan h = plan_hist(f, (size_t)lds_rows * 32 + jb + staged, lds_rows, hist_levels, want, hist_mode);   // table, couplings
   if (hist_mode == 0) {
     // the expanded table (and every level of the histogram) when it costs no resident workgroups
     const void* fx = reinterpret_cast<const void*>(&k_sweeps<L, false, false, true>);
-    const size_t lds_x = (size_t)hist_levels * 32 + jb + (size_t)hist_levels * 4;
+    const size_t lds_x = staged_base((uint32_t)((size_t)hist_levels * 32 + jb), hist_levels) + (L >= 12 ? staged_bytes<L>() : 0);
     int occ_x = 0, occ = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ_x, fx, 64, lds_x) == hipSuccess &&
         hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, f, 64, h.lds) == hipSuccess && occ_x >= std::min(occ, want)) {
       if (ws_mode != 1) {
         const size_t lds_w = (size_t)ws_ring_base(hist_levels, jk_words(L), hist_levels) + 3 * (size_t)ws_slot_bytes<L>();
-        const void* fw = spec ? reinterpret_cast<const void*>(&k_sweeps_ws<L, true>)
-                              : reinterpret_cast<const void*>(&k_sweeps_ws<L, false>);
+        const void* fw = reinterpret_cast<const void*>(&k_sweeps_ws<L>);
         int occ_w = 0;
         const bool fits = hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ_w, fw, 128, lds_w) == hipSuccess &&
                           occ_w >= want;
         if (ws_mode == 2 ? occ_w >= 1 : (fits && n_waves <= 4 * n_cu)) {
           a.hist_margin = hist_levels;
           a.hist_n = hist_levels;
-          return spec ? launch_ws<L, true>(a, n_waves, lds_w, s) : launch_ws<L, false>(a, n_waves, lds_w, s);
+          return launch_ws<L>(a, n_waves, lds_w, spec, s);
         }
       }
       if (!spec) {

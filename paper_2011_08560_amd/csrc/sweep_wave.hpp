@@ -14,7 +14,7 @@
 // (16 products and 18 xors for four random words, 6 for the decision, 1 for the running extremes,
 // the rest block preparation), 14.1 in the tempering form. Measured: L = 8 x 4096 realizations
 // 70.4 us per sweep (82 cycles per wave-attempt and SIMD; 84 us with per-site gathering products
-// and a plane index resolved by compares and selects), tempering L = 8 x 2048 30.5 us (41).
+// and a plane index resolved by compares and selects), tempering L = 8 x 2048 30.5 us (71).
 //
 // The sweep order is checkerboard: all sites of colour 0, then colour 1. The
 // neighbours of a site all have the other colour, so at the start of each
@@ -150,7 +150,7 @@ struct Window {
 // several waves per SIMD whose walkers often reach a bound (small lattices, first rounds) from
 // shorter ones.
 template <int L>
-constexpr int check_groups() { return L >= 12 ? 8 : L >= 10 ? 4 : 2; }
+constexpr int check_groups() { return L >= 10 ? 4 : 2; }
 
 __device__ __forceinline__ Window make_window(int state, int Bbot, int Btop) {
   constexpr int INF = 1 << 29;
@@ -347,23 +347,49 @@ __device__ __forceinline__ void accept_group(const u32x4& rnd, const uint32_t (&
   if constexpr (FB > H && qe % H == H - 1 && qe + 1 < Q && (((qe + 1) / H) * FB) % 32 != 0) F <<= (FB - H);
 }
 
-// Speculative form: the level and the clamped row after acceptance are computed beforehand
-// (the next site's thresholds for both outcomes are loaded meanwhile).
-__device__ __forceinline__ void accept_level_spec(uint32_t rc, uint32_t th, int Bacc, int Racc, int& B, int& R,
-                                                  uint32_t& F) {
-  int Bn, Rn;
-  uint32_t Fn;
-  asm("v_cmp_le_u32_e32 vcc, %[rc], %[th]\n\t"
-      "s_nop 1\n\t"
-      "v_cndmask_b32_e32 %[Bn], %[B], %[Bacc], vcc\n\t"
-      "v_cndmask_b32_e32 %[Rn], %[R], %[Racc], vcc\n\t"
-      "v_addc_co_u32_e32 %[Fn], vcc, %[F], %[F], vcc"
-      : [Bn] "=&v"(Bn), [Rn] "=&v"(Rn), [Fn] "=&v"(Fn)
-      : [rc] "v"(rc), [th] "v"(th), [Bacc] "v"(Bacc), [Racc] "v"(Racc), [B] "v"(B), [R] "v"(R), [F] "v"(F)
-      : "vcc");
+// Paired form: the thresholds of a site for both outcomes of the site before it (rej, acc) are read
+// before that one is decided; prev, its acceptance of all lanes, selects. The read is off the chain
+// then: two attempts share its latency. Returns this attempt's acceptance. The two instructions after
+// the comparison are the distance its mask needs: the shift of prev into F (SHIFT) and a step of the
+// running extremes (EXT as in decide_bytes) where there is one to do.
+#define NFM_PAIRED(S1, S2, ROW)                                                                     \
+  asm volatile("v_cndmask_b32_e64 %[th], %[rej], %[acc], %[prev]\n\tv_cmp_le_u32_e64 %[m], %[rc], %[th]\n\t" S1 \
+               "\n\t" S2 "\n\tv_cndmask_b32_e64 %[Bn], %[B], %[Bacc], %[m]" ROW                      \
+               : [Bn] "=&v"(Bn), [Rn] "=&v"(Rn), [th] "=&v"(th), [m] "=&s"(m), [F] "+&v"(F), [x] "+&v"(x) \
+               : [rc] "v"(rc), [rej] "v"(rej), [acc] "v"(acc), [prev] "s"(prev), [Bacc] "v"(Bacc), [B] "v"(B), \
+                 [R] "v"(R), [Racc] "v"(Racc), [t0] "v"(t0), [t1] "v"(t1)                            \
+               : "vcc")
+#define NFM_PAIRED_EXT(S1, ROW)                                                           \
+  do {                                                                                    \
+    if constexpr (EXT == 0) NFM_PAIRED(S1, "s_nop 0", ROW);                               \
+    if constexpr (EXT == 1) NFM_PAIRED(S1, "v_min3_i32 %[x], %[x], %[t0], %[t1]", ROW);   \
+    if constexpr (EXT == 2) NFM_PAIRED(S1, "v_max3_i32 %[x], %[x], %[t0], %[t1]", ROW);   \
+  } while (0)
+template <bool XT, bool SHIFT, int EXT>
+__device__ __forceinline__ uint64_t decide_paired(uint32_t rc, uint32_t rej, uint32_t acc, uint64_t prev, int Bacc,
+                                                  int Racc, int t0, int t1, int& B, int& R, uint32_t& F, int& x) {
+  int Bn, Rn = 0;
+  uint32_t th;
+  uint64_t m;
+  if constexpr (XT) {   // the row is the level
+    if constexpr (SHIFT) NFM_PAIRED_EXT("v_addc_co_u32_e64 %[F], vcc, %[F], %[F], %[prev]", "");
+    else NFM_PAIRED_EXT("s_nop 0", "");
+    R = Bn;
+  } else {              // the row moves with the level (R, Racc: clamped beforehand)
+    if constexpr (SHIFT)
+      NFM_PAIRED_EXT("v_addc_co_u32_e64 %[F], vcc, %[F], %[F], %[prev]",
+                     "\n\tv_cndmask_b32_e64 %[Rn], %[R], %[Racc], %[m]");
+    else
+      NFM_PAIRED_EXT("s_nop 0", "\n\tv_cndmask_b32_e64 %[Rn], %[R], %[Racc], %[m]");
+    R = Rn;
+  }
   B = Bn;
-  R = Rn;
-  F = Fn;
+  return m;
+}
+#undef NFM_PAIRED_EXT
+#undef NFM_PAIRED
+__device__ __forceinline__ void accept_shift(uint64_t mask, uint32_t& F) {
+  asm volatile("v_addc_co_u32_e64 %0, vcc, %0, %0, %1" : "+v"(F) : "s"(mask) : "vcc");
 }
 
 // Exchange threshold of slots (s, s+1) whose energies differ by 4d (Eq. (8)): q^d rounded down
@@ -387,6 +413,25 @@ __device__ __forceinline__ int clamp_row(int B, int Bmax) {
   return R;
 }
 
+// Where the random words come from.
+//   kGenVector   all rounds on the vector unit
+//   kGenScalar   the uniform half of rounds 0-2 on the scalar unit (free where other waves fill the
+//                vector unit meanwhile, an issue slot per instruction where a wave is alone)
+//   kGenStaged   that half for all groups of a sweep at once, one group per lane, into LDS at the
+//                sweep's start (staged_words): a group then costs one broadcast read
+//   kGenWave     a generator wave beside the sampling wave
+enum Gen { kGenVector, kGenScalar, kGenStaged, kGenWave };
+
+// kGenStaged, LDS after the histogram: per group of four sites in sweep order {hi(M0 c0) ^ k1_0,
+// hi(p) ^ k0_2, lo(p) ^ k0_3, -}, p = M1 n2 of round 2, and two entries more for the reads ahead.
+template <int L>
+__host__ __device__ constexpr uint32_t staged_bytes() {
+  return (uint32_t)(2 * Geo<L>::LB * Geo<L>::NG + 2) * 16u;
+}
+__host__ __device__ inline uint32_t staged_base(uint32_t hbase, int hist_n) {
+  return (hbase + 4u * (uint32_t)hist_n + 15u) & ~15u;
+}
+
 // PT = false: multicanonical sweeps; the table row follows the walker's level.
 // PT = true: parallel tempering (Sec. II, Eq. (8)); each wave of 64 walkers holds floor(64/M)
 // sets of M configurations (lanes g M .. g M + M - 1; the remaining lanes idle at slot 0, outside
@@ -395,7 +440,7 @@ __device__ __forceinline__ int clamp_row(int B, int Bmax) {
 // XT (multicanonical, no speculation): the table is expanded on chip to one row per level of
 // the realization (rows outside the stored range repeat its edge rows, as the clamp would), so
 // the row of a level is the level itself and the decision needs no clamp.
-template <int L, bool SPEC, bool PT, bool XT = false, bool WS = false, bool SU = false, bool ROLL = (L >= 8)>
+template <int L, bool SPEC, bool PT, bool XT, Gen GEN, bool ROLL = (L >= 8)>
 __device__ __forceinline__ void sweep_wave(const SweepArgs& A, int wave) {
   using G = Geo<L>;
   constexpr int NWP = G::NWP, Q = G::Q, N = G::N, H = G::H, FB = G::F, ZB = G::ZB, LB = G::LB, NG = G::NG;
@@ -404,6 +449,8 @@ __device__ __forceinline__ void sweep_wave(const SweepArgs& A, int wave) {
   constexpr int NBLK = 3 * NWP;
   constexpr bool kRolled = ROLL && LB > 2;
   constexpr int kZUnroll = kRolled ? 1 : LB;
+  constexpr bool PAIR = !PT && (SPEC || GEN == kGenWave);   // thresholds of both outcomes read ahead
+  constexpr bool WS = GEN == kGenWave, SU = GEN == kGenScalar, PS = GEN == kGenStaged;
   static_assert(!(PT && SPEC), "the tempering row does not depend on the decision");
   static_assert(!(XT && PT), "the expanded table is for the multicanonical form");
   static_assert(!(XT && SPEC) || WS, "the speculative form with the expanded table runs beside a generator wave");
@@ -541,7 +588,7 @@ __device__ __forceinline__ void sweep_wave(const SweepArgs& A, int wave) {
   // the per-plane coupling words and constants without spilling scalar registers. (Not needed
   // when a generator wave supplies the words.)
   PhiloxKeysV kv;
-  if constexpr (!WS) kv = philox_round_keys_v(key0, key1);
+  if constexpr (!WS) kv = philox_round_keys_v<SU || PS ? 3 : 0>(key0, key1);
   uint32_t ctr3 = ((uint32_t)wl << 8) | (PT ? kTagPT : kTagAcc);
 
   // Level steps of the sites of block (c, z) from the other colour's spins and the couplings: the
@@ -637,16 +684,52 @@ __device__ __forceinline__ void sweep_wave(const SweepArgs& A, int wave) {
     return PhiloxRun{((uint32_t)(c * L + z * ZB + g / G::NGP) << 8) | (uint32_t)(g % G::NGP), (uint32_t)t, real_id, ctr3};
   };
   // first generator round of the next group that runs beside attempt i of a group
-  constexpr auto round_of = [](int i) constexpr { return SU ? (i == 0 ? 0 : 2 + 2 * i) : (i < 3 ? 3 * i - i / 2 : 2 + 2 * i); };
+  constexpr auto round_of = [](int i) constexpr { return SU || PS ? (i == 0 ? 0 : 2 + 2 * i) : (i < 3 ? 3 * i - i / 2 : 2 + 2 * i); };
   static_assert(round_of(0) == 0 && round_of(4) == 10, "ten rounds a group");
   // The generator runs one group ahead: pr holds the words of the next group of four sites, and
-  // its rounds are spread over the attempts of the group before it (also across blocks, colours
-  // and sweeps), so that they fill the wait for each threshold read.
+  // its rounds are spread over the attempts of the group before it (also across blocks and colours,
+  // and but for the staged form across sweeps), so that they fill the wait for each threshold read.
   PhiloxRun pr{};
-  if constexpr (!WS) {
+  if constexpr (!WS && !PS) {
     pr = group_ctr(0, 0, 0, A.t0);
-    philox_rounds<0, 10>(pr, kv);
+    if constexpr (SU) philox_rounds_u<0, 3>(pr, key0, key1);
+    philox_rounds<SU ? 3 : 0, 10>(pr, kv);
   }
+  // Staged form. With c0, t, real_id uniform and c3 the walker's word, rounds 0-2 leave: n2 = A ^ c3,
+  // q = M1 n2, n0' = hi(q) ^ K1, r = M0 n0', n0'' = lo(q) ^ X2, n2'' = hi(r) ^ P3, n3'' = lo(r), and
+  // round 3's first word takes X3 for its uniform part; A, X2, X3 are the staged words, K1 is
+  // constant and P3 constant in a sweep.
+  constexpr uint32_t PM0 = 0xD2511F53u, PM1 = 0xCD9E8D57u, PW0 = 0x9E3779B9u, PW1 = 0xBB67AE85u;
+  const uint32_t sbase = PS ? staged_base(hbase, PT ? 0 : hn) : 0u;
+  uint32_t ps_K1 = 0, ps_P3 = 0, ps_addr = 0;   // ps_addr: staged words of the current block
+  u32x4 ps_next{};                              // staged words of the next group
+  if constexpr (PS) ps_K1 = (PM1 * real_id) ^ (key0 + PW0);
+  auto stage_sweep = [&](uint64_t t) __attribute__((always_inline)) {
+    const uint32_t n0 = __umulhi(PM1, real_id) ^ (uint32_t)t ^ key0;
+    const uint32_t H0 = __umulhi(PM0, n0) ^ (key1 + PW1);
+    ps_P3 = (PM0 * n0) ^ (key1 + 2u * PW1);
+    for (int e = lane; e < 2 * LB * NG; e += 64) {
+      const int cb = e / NG, g = e % NG;   // block c LB + b, group within it
+      const uint32_t c0 = ((uint32_t)(cb * ZB + g / G::NGP) << 8) | (uint32_t)(g % G::NGP);
+      const uint64_t p0 = (uint64_t)PM0 * c0;
+      const uint64_t p = (uint64_t)PM1 * (H0 ^ (uint32_t)p0);
+      const u32x4 w{{(uint32_t)(p0 >> 32) ^ key1, (uint32_t)(p >> 32) ^ (key0 + 2u * PW0),
+                     (uint32_t)p ^ (key0 + 3u * PW0), 0u}};
+      lds_store_u32x4(sbase + (uint32_t)e * 16u, w);
+    }
+    asm volatile("" ::: "memory");
+  };
+  // rounds 0-3 of the group whose staged words are w
+  auto staged_rounds = [&](const u32x4& w) __attribute__((always_inline)) {
+    const uint64_t q = (uint64_t)PM1 * (w.v[0] ^ ctr3);
+    const uint64_t r = (uint64_t)PM0 * ((uint32_t)(q >> 32) ^ ps_K1);
+    const uint64_t p0 = (uint64_t)PM0 * ((uint32_t)q ^ w.v[1]);
+    const uint64_t p1 = (uint64_t)PM1 * ((uint32_t)(r >> 32) ^ ps_P3);
+    pr.c0 = (uint32_t)(p1 >> 32) ^ w.v[2];
+    pr.c1 = (uint32_t)p1;
+    pr.c2 = xor3((uint32_t)(p0 >> 32), (uint32_t)r, kv.k1[3]);
+    pr.c3 = (uint32_t)p0;
+  };
   // Warp-specialized form: the words of block b sit in ring slot b mod 3; rw holds the next
   // group's words, read one group ahead.
   const uint32_t rbase = WS ? ws_ring_base(K, jk_words(L), hn) : 0u;
@@ -671,10 +754,19 @@ __device__ __forceinline__ void sweep_wave(const SweepArgs& A, int wave) {
   for (uint32_t s = 0; s < A.n_sweeps; ++s) {
     const uint64_t t = A.t0 + s;
     const uint64_t tau0 = t * (uint64_t)N + 1u;
-    // The counter is opaque in each sweep where planes are unrolled beyond L = 4, and in the persistent
-    // kernel: products that depend on the group and the walker alone would otherwise be kept in
+    if constexpr (PS) {
+      // this sweep's staged words, then the first group's random words (not run ahead across sweeps:
+      // the table holds one sweep)
+      stage_sweep(t);
+      ps_addr = sbase;
+      staged_rounds(lds_load_u32x4(ps_addr));
+      philox_rounds<4, 10>(pr, kv);
+      ps_next = lds_load_u32x4(ps_addr + 16u);
+    }
+    // The counter is opaque in each sweep where planes are unrolled beyond L = 4, in the tempering form
+    // and in the persistent kernel: products that depend on the group and the walker alone would otherwise be kept in
     // registers for all groups (L = 6: over 256 of them, one wave per SIMD).
-    if constexpr (ROLL || L == 6) asm volatile("" : "+v"(ctr3));
+    if constexpr (ROLL || L == 6 || PT) asm volatile("" : "+v"(ctr3));
     int es0 = 0, es1 = 0, es2 = 0;   // tempering: bit counts of the accepted steps' planes
     static_for<2>([&](auto cc) __attribute__((always_inline)) {
       constexpr int c = decltype(cc)::value;
@@ -693,7 +785,9 @@ __device__ __forceinline__ void sweep_wave(const SweepArgs& A, int wave) {
       // (tempering: a group ahead within a block)
       uint32_t th_fly = 0, addr_cur = 0;
       uint32_t thg[4] = {0, 0, 0, 0};   // tempering: the thresholds of the group to come
-      if constexpr (!PT && !SPEC) th_fly = read_row(or_entry<0>(first_entry(Vc), R));
+      if constexpr (!PT) th_fly = read_row(or_entry<0>(first_entry(Vc), R));
+      uint32_t th_acc = th_fly;   // paired form: th_fly after a rejection, th_acc after an acceptance
+      uint64_t accepted = 0;      // of the attempt before
       // thresholds of group g of a block (byte words of its string word)
       auto group_thresholds = [&](const uint32_t (&Aw)[8], auto gt) __attribute__((always_inline)) {
         constexpr int g = decltype(gt)::value;
@@ -729,12 +823,6 @@ __device__ __forceinline__ void sweep_wave(const SweepArgs& A, int wave) {
         // levels after each attempt since the last window check (kCheckGroups groups of four)
         constexpr int kCheckGroups = check_groups<L>();
         int Bq[4 * kCheckGroups];
-        // speculative form: the pair for site 0 of the block is loaded at the block's start
-        uint32_t p_rej = 0, p_acc = 0;
-        int Racc_prev = R;
-        if constexpr (SPEC && !PT) {
-          p_rej = p_acc = read_row(or_entry<0>(Ac[0], R));
-        }
         static_for<NG>([&](auto gc) __attribute__((always_inline)) {
           constexpr int g = decltype(gc)::value;
           u32x4 rnd;
@@ -746,7 +834,8 @@ __device__ __forceinline__ void sweep_wave(const SweepArgs& A, int wave) {
           } else {
             rnd = u32x4{{pr.c0, pr.c1, pr.c2, pr.c3}};
             // the next group: in this block, the next block, the other colour or the next sweep
-            if (g + 1 < NG) pr = group_ctr(c, z, g + 1, t);
+            if constexpr (PS) {}
+            else if (g + 1 < NG) pr = group_ctr(c, z, g + 1, t);
             else if (has_next) pr = group_ctr(c, z + 1, 0, t);
             else if (c == 0) pr = group_ctr(1, 0, 0, t);
             else pr = group_ctr(0, 0, 0, t + 1);
@@ -772,6 +861,11 @@ __device__ __forceinline__ void sweep_wave(const SweepArgs& A, int wave) {
             if constexpr (SU) {
               philox_rounds_u<0, 3>(pr, key0, key1);
               philox_rounds<3, 10>(pr, kv);
+            } else if constexpr (PS) {
+              const u32x4 w = ps_next;
+              ps_next = lds_load_u32x4(ps_addr + (uint32_t)(g + 2) * 16u);
+              staged_rounds(w);
+              philox_rounds<4, 10>(pr, kv);
             } else {
               philox_rounds<0, 10>(pr, kv);
             }
@@ -804,32 +898,46 @@ __device__ __forceinline__ void sweep_wave(const SweepArgs& A, int wave) {
                 if constexpr (SU && i == 0) {
                   philox_rounds_u<0, 3>(pr, key0, key1);
                   philox_rounds<3, 4>(pr, kv);
+                } else if constexpr (PS && i == 0) {
+                  const u32x4 w = ps_next;
+                  ps_next = lds_load_u32x4(ps_addr + (uint32_t)(g + 2) * 16u);
+                  staged_rounds(w);
                 } else {
                   philox_rounds<round_of(i), round_of(i + 1)>(pr, kv);
                 }
               }
             };
-            if constexpr (SPEC && !PT) {
+            if constexpr (PAIR) {
               const uint32_t rc = rnd.v[i];
-              rounds();
-              // thresholds of site q+1 for both outcomes of q are loaded before q is decided; the
-              // threshold of site q is picked from the pair loaded one site earlier
               const int Bacc = add_step(B, Dc[p & 7], (p >> 3) & 3);
-              uint32_t n_rej = 0, n_acc = 0;
+              const int Racc = XT ? Bacc : clamp_row(Bacc, Bmax);
               if constexpr (last_in_word && q + 1 < Q) {
                 expand(Vc, wn, Ac, Dc);
                 if constexpr (wn == NWP - 1) prepare_next();
               }
-              const int Racc = XT ? Bacc : clamp_row(Bacc, Bmax);
-              if constexpr (q + 1 < Q) {
-                n_rej = read_row(or_entry<(pn >> 3) & 3>(Ac[pn & 7], R));
-                n_acc = read_row(or_entry<(pn >> 3) & 3>(Ac[pn & 7], Racc));
+              const uint32_t Aq = q + 1 < Q ? Ac[pn & 7] : An;
+              uint32_t n_rej = 0, n_acc = 0;
+              if (q + 1 < Q || has_next) {
+                n_rej = read_row(or_entry<(pn >> 3) & 3>(Aq, R));
+                n_acc = read_row(or_entry<(pn >> 3) & 3>(Aq, Racc));
               }
-              const uint32_t th_cur = (R == Racc_prev) ? p_acc : p_rej;
-              accept_level_spec(rc, th_cur, Bacc, Racc, B, R, F);
-              p_rej = n_rej;
-              p_acc = n_acc;
-              Racc_prev = Racc;
+              __builtin_amdgcn_sched_barrier(0);   // the reads go out before anything else
+              rounds();
+              // the attempt before is shifted into F here, but for the last of a row with unused bits
+              // and of a word, which are shifted in at once
+              constexpr bool kAtOnce = last_in_word || (j == H - 1 && FB > H);
+              constexpr bool kShift = q > 0 && j > (FB > H ? 0 : -1) && (p & 31) > 0;
+              if constexpr (a >= 2 && a % 2 == 0)
+                accepted = decide_paired<XT, kShift, 1>(rc, th_fly, th_acc, accepted, Bacc, Racc, Bq[a - 2], Bq[a - 1], B,
+                                                        R, F, bmin);
+              else if constexpr (a >= 3)
+                accepted = decide_paired<XT, kShift, 2>(rc, th_fly, th_acc, accepted, Bacc, Racc, Bq[a - 3], Bq[a - 2], B,
+                                                        R, F, bmax);
+              else
+                accepted = decide_paired<XT, kShift, 0>(rc, th_fly, th_acc, accepted, Bacc, Racc, B, B, B, R, F, bmin);
+              if constexpr (kAtOnce) accept_shift(accepted, F);
+              th_fly = n_rej;
+              th_acc = n_acc;
             } else {
               // (1) the threshold of this site, read by the previous decision at the address it
               //     computed
@@ -845,12 +953,10 @@ __device__ __forceinline__ void sweep_wave(const SweepArgs& A, int wave) {
               //     rounds' outputs pass through the second one. The first takes only the words
               //     the round's products do not read: a VALU read of a register an asm statement
               //     wrote costs a wait state, and uniform words stay scalar.
-              if constexpr (!WS) {
-                if (!SU || i > 0) asm volatile("" : "+v"(pr.c1), "+v"(pr.c3));
-              }
+              if constexpr ((!SU && !PS) || i > 0) asm volatile("" : "+v"(pr.c1), "+v"(pr.c3));
               rounds();
               const uint32_t rc = rnd.v[i];
-              if constexpr (!WS) asm volatile("" : "+v"(pr.c0), "+v"(pr.c1), "+v"(pr.c2), "+v"(pr.c3));
+              asm volatile("" : "+v"(pr.c0), "+v"(pr.c1), "+v"(pr.c2), "+v"(pr.c3));
               // (3) the decision, the next site's table address and its read, issued before the
               //     bookkeeping and flips that follow
               constexpr int cb = (p >> 3) & 3, nb = (pn >> 3) & 3;
@@ -880,13 +986,9 @@ __device__ __forceinline__ void sweep_wave(const SweepArgs& A, int wave) {
           if constexpr (g % kCheckGroups == kCheckGroups - 1 || g + 1 == NG) {
             constexpr int g0 = g - g % kCheckGroups;                   // first group since the check
             constexpr int cnt = 4 * (g - g0) + n_att;                  // attempts since the check (even)
-            // the decisions have taken in the levels of all attempts but the last pair (not the
-            // speculative form's)
-#pragma unroll
-            for (int k = SPEC ? 0 : cnt - 2; k < cnt; k += 2) {
-              bmin = min(bmin, min(Bq[k], Bq[k + 1]));
-              bmax = max(bmax, max(Bq[k], Bq[k + 1]));
-            }
+            // the decisions have taken in the levels of all attempts but the last pair
+            bmin = min(bmin, min(Bq[cnt - 2], Bq[cnt - 1]));
+            bmax = max(bmax, max(Bq[cnt - 2], Bq[cnt - 1]));
             if (bmin < win.lo || bmax > win.hi) {
 #pragma unroll
               for (int k = 0; k < cnt; ++k)
@@ -899,6 +1001,7 @@ __device__ __forceinline__ void sweep_wave(const SweepArgs& A, int wave) {
         });
 #pragma unroll
         for (int w = 0; w < NWP; ++w) lat(c, w)[z] = Cw[w];
+        if constexpr (PS) ps_addr += 16u * NG;
         if constexpr (WS) {
           // this block's words are consumed: the generator may refill their slot
           __syncthreads();
@@ -938,7 +1041,7 @@ __device__ __forceinline__ void sweep_wave(const SweepArgs& A, int wave) {
         const int d = (Eh - E) / 4;   // energies of one realization share their residue mod 4
         const uint32_t th = pt_swap_threshold(A.pt_q[(int64_t)r * kMaxReplicas + slot], d);
         const uint32_t set = pt_set;   // set index within the realization
-        const u32x4 rr = philox4x32_10_vk((uint32_t)(slot >> 2), (uint32_t)t, real_id, (set << 8) | kTagSwap, kv);
+        const u32x4 rr = philox4x32_10((uint32_t)(slot >> 2), (uint32_t)t, real_id, (set << 8) | kTagSwap, key0, key1);
         const int k4 = slot & 3;
         const uint32_t rw = k4 == 0 ? rr.v[0] : k4 == 1 ? rr.v[1] : k4 == 2 ? rr.v[2] : rr.v[3];
         dec = min(rw, 0xFFFFFFFEu) < th ? 1 : 0;
