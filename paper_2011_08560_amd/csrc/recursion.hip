@@ -9,8 +9,13 @@
 // target profile): for consecutive visited levels k < k',
 //   est = [ln H(k') - lnW(k')] - [ln H(k) - lnW(k)],  g0 = H(k) H(k') / (H(k) + H(k')),
 //   p(k) += g0,  b(k) += (g0 / p(k)) (est - (b(k) + ... + b(k'-1))).
-// The sequential parts (prefix sums over levels) run on one thread per realization in the same
-// operation order as the oracle; the table is built by all threads of the block.
+//
+// One block per realization. What is a chain keeps the oracle's operation order on one thread: the
+// prefix S, the flatness sum and the 1/k normalization, each over values staged in LDS (a step is one
+// dependent FP64 addition beside reads that run ahead). Everything else is a level or a table entry
+// per thread: the logarithms and exponentials, and the step updates, since consecutive visited levels
+// k < k' touch only b(k), ..., b(k' - 1) and p(k). L = 8 x 1024 realizations: 610 us on one thread per
+// realization from device memory, 34 us so.
 #include "kernels.hpp"
 #include "table_builder.hpp"
 
@@ -20,38 +25,115 @@ __device__ __forceinline__ double rec_lnP_power(double E, double E_g, double dE,
   return alpha * log(E / (dE - E_g) + 1.0);
 }
 
-// S, ln P and lnW on [k_lo, k_top] from b (one thread); with a seeded prior also on
-// [k_seed, k_lo): S continues with the seeded steps under the frozen profile lnP(k_lo).
-__device__ void rec_weights_seq(const RecInfo& ri, int e_base, const double* b, double* S, double* lnP, double* lnW) {
-  const int k_lo = ri.k_lo, k_top = ri.k_top;
-  S[k_top] = 0.0;
-  for (int k = k_top - 1; k >= k_lo; --k) S[k] = S[k + 1] - b[k];
-  const double E_g = (double)(e_base + 4 * k_lo);
-  double acc = 0.0;
-  for (int k = k_lo; k <= k_top; ++k) {
-    const double E = (double)(e_base + 4 * k);
-    double lp;
-    if (ri.profile == 0) {
-      lp = 0.0;
-    } else if (ri.profile == 1) {
-      lp = rec_lnP_power(E, E_g, ri.pl_dE, ri.pl_alpha);
-    } else {
-      if (k == k_lo) {
-        acc = S[k];
-      } else {
-        const double m = acc > S[k] ? acc : S[k];
-        acc = m + log1p(exp(-fabs(acc - S[k])));
-      }
-      lp = S[k] - acc;
+// The chains are staged kChunk levels at a time (all of a lattice's up to L = 10 at once; L = 12 has
+// about 730 on [k_lo, k_top]). 12 KB for both arrays leaves the block count per compute unit to the
+// waves.
+constexpr int kChunk = 768;
+struct RecShared {
+  alignas(16) double s[kChunk], v[kChunk];
+};
+
+// acc <- acc + sign x(i) for i = 0 ... n - 1 in order, in 16-byte reads eight elements ahead of the
+// additions; KEEP stores the running value in the element's place. Elements up to the next multiple
+// of eight must hold 0 (adding it changes nothing).
+template <bool SUB, bool KEEP>
+__device__ __forceinline__ double rec_chain(double* x, int n, double acc) {
+  static_assert(kChunk % 8 == 0, "chunks of whole batches");
+  double2* q = reinterpret_cast<double2*>(x);
+  double2 cur[4], nxt[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) cur[i] = q[i];
+  for (int j = 0; j < n; j += 8, q += 4) {
+    const int ahead = j + 8 < n ? 4 : 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) nxt[i] = q[ahead + i];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      acc = SUB ? acc - cur[i].x : acc + cur[i].x;
+      cur[i].x = acc;
+      acc = SUB ? acc - cur[i].y : acc + cur[i].y;
+      cur[i].y = acc;
     }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      if constexpr (KEEP) q[i] = cur[i];
+      cur[i] = nxt[i];
+    }
+  }
+  return acc;
+}
+
+// Stages b's steps of the c-th chunk of [low, k_top] counted from above, one place per level from
+// k_top down; place 0 of the first chunk is S(k_top) = 0. Returns the number of levels.
+__device__ __forceinline__ int rec_stage_steps(RecShared& sh, const double* b, int low, int k_top, int c) {
+  const int n = min(k_top - low + 1 - c * kChunk, kChunk);
+  for (int i = threadIdx.x; i < ((n + 7) & ~7); i += blockDim.x) {
+    const int k = k_top - c * kChunk - i;
+    sh.s[i] = i < n && k < k_top ? b[k] : 0.0;
+  }
+  return n;
+}
+
+// ln P and lnW on [low, k_top] from S (all threads; S visible to them). With a seeded prior also on
+// [k_seed, k_lo), where S continues with the seeded steps under the frozen profile lnP(k_lo).
+__device__ void rec_profile_block(RecShared& sh, const RecInfo& ri, int e_base, const double* S, double* lnP,
+                                  double* lnW) {
+  const int k_lo = ri.k_lo, k_top = ri.k_top, low = rec_low(ri);
+  const double E_g = (double)(e_base + 4 * k_lo);
+  auto power = [&](int k) { return rec_lnP_power((double)(e_base + 4 * k), E_g, ri.pl_dE, ri.pl_alpha); };
+  double lp_lo = 0.0;   // lnP(k_lo)
+  if (ri.profile == 1) {
+    lp_lo = power(k_lo);
+  } else if (ri.profile != 0) {
+    double acc = 0.0;
+    for (int c0 = k_lo; c0 <= k_top; c0 += kChunk) {
+      const int n = min(k_top - c0 + 1, kChunk);
+      __syncthreads();
+      for (int i = threadIdx.x; i < n; i += blockDim.x) sh.v[i] = S[c0 + i];
+      __syncthreads();
+      if (threadIdx.x == 0) {
+        for (int i = 0; i < n; ++i) {
+          const double Sk = sh.v[i];
+          if (c0 + i == k_lo) {
+            acc = Sk;
+          } else {
+            const double m = acc > Sk ? acc : Sk;
+            acc = m + log1p(exp(-fabs(acc - Sk)));
+          }
+          sh.v[i] = Sk - acc;
+        }
+      }
+      __syncthreads();
+      for (int i = threadIdx.x; i < n; i += blockDim.x) {
+        const double lp = sh.v[i];
+        lnP[c0 + i] = lp;
+        lnW[c0 + i] = -S[c0 + i] + lp;
+      }
+    }
+    lp_lo = S[k_lo] - S[k_lo];
+  }
+  for (int k = low + (int)threadIdx.x; k <= k_top; k += blockDim.x) {
+    if (k >= k_lo && ri.profile != 0 && ri.profile != 1) break;
+    const double lp = k > k_lo && ri.profile == 1 ? power(k) : lp_lo;
     lnP[k] = lp;
     lnW[k] = -S[k] + lp;
   }
-  for (int k = k_lo - 1; k >= rec_low(ri); --k) {
-    S[k] = S[k + 1] - b[k];
-    lnP[k] = lnP[k_lo];
-    lnW[k] = -S[k] + lnP[k];
+}
+
+// S, ln P and lnW from b (all threads; b visible to them).
+__device__ void rec_weights_block(RecShared& sh, const RecInfo& ri, int e_base, const double* b, double* S,
+                                  double* lnP, double* lnW) {
+  const int k_top = ri.k_top, low = rec_low(ri);
+  double acc = 0.0;   // thread 0's
+  for (int c = 0; c * kChunk <= k_top - low; ++c) {
+    const int n = rec_stage_steps(sh, b, low, k_top, c);
+    __syncthreads();
+    if (threadIdx.x == 0) acc = rec_chain<true, true>(sh.s, n, acc);
+    __syncthreads();
+    for (int i = threadIdx.x; i < n; i += blockDim.x) S[k_top - c * kChunk - i] = sh.s[i];
+    __syncthreads();
   }
+  rec_profile_block(sh, ri, e_base, S, lnP, lnW);
 }
 
 // One realization per block: weights from the current estimate, table, round-trip bounds.
@@ -60,15 +142,16 @@ __global__ void k_rec_weights(RealInfo* __restrict__ reals, RecInfo* __restrict_
   RealInfo* rp = reals + blockIdx.x;
   RecInfo* rc = recs + blockIdx.x;
   const int64_t off = rp->level_off;
-  if (threadIdx.x == 0) {
-    rec_weights_seq(*rc, rp->e_base, A.b + off, A.S + off, A.lnP + off, A.lnW + off);
-    if (set_bounds) {
-      rp->e_bot = rp->e_base + 4 * rc->k_lo;
-      rp->e_top = 0;
-    }
+  __shared__ RecShared sh;
+  const RecInfo ri = *rc;
+  const int e_base = rp->e_base;
+  rec_weights_block(sh, ri, e_base, A.b + off, A.S + off, A.lnP + off, A.lnW + off);
+  if (threadIdx.x == 0 && set_bounds) {
+    rp->e_bot = e_base + 4 * ri.k_lo;
+    rp->e_top = 0;
   }
   __syncthreads();
-  build_table_block(rp, A.lnW + off, rec_low(*rc), rc->k_top, tables);
+  build_table_block(rp, A.lnW + off, rec_low(ri), ri.k_top, tables);
 }
 
 // Initial state: b = p = 0, nothing visited, k_lo = lowest level of any walker's minimum.
@@ -112,104 +195,161 @@ __global__ void k_rec_init(RealInfo* __restrict__ reals, RecInfo* __restrict__ r
 }
 
 // One update from the histogram of the last sampling round, then the next weights and table.
-__global__ void k_rec_update(RealInfo* __restrict__ reals, RecInfo* __restrict__ recs, RecArrays A, WalkerState ws,
-                             unsigned long long* __restrict__ hist, uint32_t* __restrict__ tables, double f_tol) {
+// Bound by memory latency (about ten dependent round trips) and the two chains, the prefix S on the
+// first wave's first lane beside the flatness sum on the second's.
+__global__ void __launch_bounds__(256) k_rec_update(RealInfo* __restrict__ reals, RecInfo* __restrict__ recs,
+                                                    RecArrays A, WalkerState ws, unsigned long long* __restrict__ hist,
+                                                    uint32_t* __restrict__ tables, double f_tol) {
   RealInfo* rp = reals + blockIdx.x;
   RecInfo* rc = recs + blockIdx.x;
   const int64_t off = rp->level_off;
-  __shared__ int s_min;
-  if (threadIdx.x == 0) s_min = 0x7fffffff;
+  const RecInfo ri = *rc;
+  const int e_base = rp->e_base, tid = threadIdx.x;
+  unsigned long long* H = hist + off;
+  double* b = A.b + off;
+  double* p = A.p + off;
+  const double* lnW = A.lnW + off;
+  const double* lnP = A.lnP + off;
+  unsigned char* visited = A.visited + off;
+  const int k_lo_used = ri.k_lo, k_top = ri.k_top;
+  __shared__ RecShared sh;
+  constexpr int kCap = level_capacity(kMaxL * kMaxL * kMaxL);
+  __shared__ unsigned long long s_hit[(kCap + 63) / 64];   // levels with counts
+  __shared__ int s_min, s_n;
+  __shared__ unsigned long long s_vmin;                    // (not negative: ordered as integers)
+  if (tid == 0) {
+    s_min = 0x7fffffff;
+    s_n = 0;
+    s_vmin = 0x7ff0000000000000ull;
+  }
   __syncthreads();
   int mn = 0x7fffffff;
-  for (int w = threadIdx.x; w < rp->walkers; w += blockDim.x) mn = min(mn, ws.E_min[rp->walker_off + w]);
-  atomicMin(&s_min, mn);
+  for (int w = tid; w < rp->walkers; w += blockDim.x) mn = min(mn, ws.E_min[rp->walker_off + w]);
+  for (int o = 32; o > 0; o >>= 1) mn = min(mn, __shfl_xor(mn, o));
+  if ((tid & 63) == 0) atomicMin(&s_min, mn);
+  for (int k0 = tid & ~63; k0 <= k_top; k0 += blockDim.x) {
+    const int k = k0 + (tid & 63);
+    const unsigned long long hit = __ballot(k <= k_top && H[k] != 0);
+    if ((tid & 63) == 0) s_hit[k0 / 64] = hit;
+  }
   __syncthreads();
-  if (threadIdx.x == 0) {
-    const unsigned long long* H = hist + off;
-    double* b = A.b + off;
-    double* p = A.p + off;
-    const double* lnW = A.lnW + off;
-    const double* lnP = A.lnP + off;
-    unsigned char* visited = A.visited + off;
-    const int k_lo_used = rc->k_lo, k_top = rc->k_top;
-    const bool seeded = rc->k_seed >= 0;
-    int k_min_seen = (s_min - rp->e_base) / 4;
-    if (k_min_seen > k_lo_used) k_min_seen = k_lo_used;
-    const int k_lo = k_min_seen;
-    // new levels: the lowest known step (plain) or their seeded steps, no accumulated weight
-    for (int k = k_lo; k < k_lo_used; ++k) {
-      if (!seeded) b[k] = b[k_lo_used];
+  const int k_lo = min((s_min - e_base) / 4, k_lo_used);
+  // new levels: the lowest known step (plain) or their seeded steps, no accumulated weight
+  if (k_lo < k_lo_used) {
+    for (int k = k_lo + tid; k < k_lo_used; k += blockDim.x) {
+      if (ri.k_seed < 0) b[k] = b[k_lo_used];
       p[k] = 0.0;
     }
-    // weights used while sampling: stored on [low, k_top], continued with the lowest step below
-    const int low = rec_low(*rc);
-    const double d_lo = (low < k_top) ? lnW[low + 1] - lnW[low] : 0.0;
-    auto lnw_at = [&](int k) {
-      return k >= low ? lnW[k] : lnW[low] - (double)(low - k) * d_lo;
-    };
-    auto lnp_at = [&](int k) { return k >= k_lo_used ? lnP[k] : lnP[k_lo_used]; };
-    int prev = -1;
-    for (int k = k_lo; k <= k_top; ++k) {
-      if (H[k] == 0) continue;
-      if (prev >= 0) {
-        const double Hk = (double)H[prev], Hk1 = (double)H[k];
-        const double est = (log(Hk1) - lnw_at(k)) - (log(Hk) - lnw_at(prev));
-        double span = 0.0;
-        for (int j = prev; j < k; ++j) span += b[j];
-        const double g0 = Hk * Hk1 / (Hk + Hk1);
-        p[prev] += g0;
-        b[prev] += (g0 / p[prev]) * (est - span);
+    __syncthreads();
+  }
+  // weights used while sampling: stored on [low, k_top], continued with the lowest step below
+  const int low = rec_low(ri);
+  const double d_lo = (low < k_top) ? lnW[low + 1] - lnW[low] : 0.0;
+  auto lnw_at = [&](int k) {
+    return k >= low ? lnW[k] : lnW[low] - (double)(low - k) * d_lo;
+  };
+  for (int k = k_lo + tid; k <= k_top; k += blockDim.x) {
+    if (!(s_hit[k >> 6] >> (k & 63) & 1ull)) continue;
+    int q = (k + 1) >> 6;   // the next level with counts
+    if (q > k_top >> 6) continue;
+    unsigned long long rest = s_hit[q] >> ((k + 1) & 63) << ((k + 1) & 63);
+    while (rest == 0ull && q < k_top >> 6) rest = s_hit[++q];
+    if (rest == 0ull) continue;
+    const int kn = q * 64 + __builtin_ctzll(rest);
+    const double Hk = (double)H[k], Hk1 = (double)H[kn];
+    const double est = (log(Hk1) - lnw_at(kn)) - (log(Hk) - lnw_at(k));
+    double span = 0.0;
+    for (int j = k; j < kn; ++j) span += b[j];
+    const double g0 = Hk * Hk1 / (Hk + Hk1);
+    const double pk = p[k] + g0;
+    p[k] = pk;
+    b[k] += (g0 / pk) * (est - span);
+  }
+  __syncthreads();
+  // flatness of H / P over the levels ever visited; S from the new steps
+  RecInfo rn = ri;
+  rn.k_lo = k_lo;
+  const int low_new = rec_low(rn);
+  const double lp_lo = lnP[k_lo_used];
+  double sum = 0.0, acc = 0.0;   // the second and the first wave's first lane
+  double vmin = __builtin_inf();
+  int nvis = 0;
+  for (int c = 0; c * kChunk <= k_top - low_new; ++c) {
+    const int nv = min(k_top - k_lo + 1 - c * kChunk, kChunk);   // (below the other range: none, or negative)
+    for (int i = tid; i < ((nv + 7) & ~7); i += blockDim.x) {
+      const int k = k_lo + c * kChunk + i;
+      double v = 0.0;
+      if (i < nv) {
+        const unsigned long long h = H[k];
+        if (h > 0) visited[k] = 1;
+        if (h > 0 || visited[k]) {
+          v = (double)h / exp(k >= k_lo_used ? lnP[k] : lp_lo);
+          vmin = v < vmin ? v : vmin;
+          ++nvis;
+        }
       }
-      prev = k;
+      sh.v[i] = v;
     }
-    double mnv = 0.0, sum = 0.0;
-    int n = 0;
-    for (int k = k_lo; k <= k_top; ++k) {
-      if (H[k] > 0) visited[k] = 1;
-      if (!visited[k]) continue;
-      const double v = (double)H[k] / exp(lnp_at(k));
-      if (n == 0 || v < mnv) mnv = v;
-      sum += v;
-      ++n;
-    }
-    const double flat = (n > 0 && sum > 0.0) ? mnv / (sum / (double)n) : 0.0;
+    const int n = rec_stage_steps(sh, b, low_new, k_top, c);
+    __syncthreads();
+    if (tid == 0) acc = rec_chain<true, true>(sh.s, n, acc);
+    if (tid == 64) sum = rec_chain<false, false>(sh.v, nv, sum);
+    __syncthreads();
+    for (int i = tid; i < n; i += blockDim.x) A.S[off + k_top - c * kChunk - i] = sh.s[i];
+    __syncthreads();
+  }
+  for (int o = 32; o > 0; o >>= 1) {
+    const double other = __shfl_xor(vmin, o);
+    vmin = other < vmin ? other : vmin;
+    nvis += __shfl_xor(nvis, o);
+  }
+  if ((tid & 63) == 0) {
+    atomicMin(&s_vmin, (unsigned long long)__double_as_longlong(vmin));
+    atomicAdd(&s_n, nvis);
+  }
+  __syncthreads();
+  if (tid == 64) {
+    const double flat = (s_n > 0 && sum > 0.0) ? __longlong_as_double((long long)s_vmin) / (sum / (double)s_n) : 0.0;
     rc->k_lo_changed = (k_lo != k_lo_used);
     rc->k_lo = k_lo;
     rc->flatness = flat;
     rc->converged = (flat >= f_tol && k_lo == k_lo_used) ? 1 : 0;
-    rc->iterations += 1;
-    // next weights (re-anchored profile), bounds for the next round
-    rec_weights_seq(*rc, rp->e_base, b, A.S + off, A.lnP + off, A.lnW + off);
-    rp->e_bot = rp->e_base + 4 * k_lo;
+    rc->iterations = ri.iterations + 1;
+    // bounds for the next round
+    rp->e_bot = e_base + 4 * k_lo;
     rp->e_top = 0;
   }
+  // next weights (re-anchored profile)
+  rec_profile_block(sh, rn, e_base, A.S + off, A.lnP + off, A.lnW + off);
   __syncthreads();
-  build_table_block(rp, A.lnW + off, rec_low(*rc), rc->k_top, tables);
+  build_table_block(rp, A.lnW + off, low_new, k_top, tables);
   const int cap = level_capacity(rp->N);
-  for (int k = threadIdx.x; k < cap; k += blockDim.x) hist[off + k] = 0ull;
+  for (int k = tid; k < cap; k += blockDim.x) H[k] = 0ull;
 }
 
 // Production weights from the final estimate (Sec. II: the DOS is determined once and reused by
 // every ensemble): flat lnW = -S, power law -S + ln P_SH, 1/k -S + (S - ln sum exp S).
 __global__ void k_rec_production(RealInfo* __restrict__ reals, RecInfo* __restrict__ recs, RecArrays A,
                                  uint32_t* __restrict__ tables, int profile, double pl_dE, double pl_alpha) {
-  if (threadIdx.x == 0) {
-    RecInfo* rc = recs + blockIdx.x;
-    rc->profile = profile;
-    rc->pl_dE = pl_dE;
-    rc->pl_alpha = pl_alpha;
-  }
-  __syncthreads();
   RealInfo* rp = reals + blockIdx.x;
   RecInfo* rc = recs + blockIdx.x;
   const int64_t off = rp->level_off;
+  __shared__ RecShared sh;
+  RecInfo ri = *rc;
+  ri.profile = profile;
+  ri.pl_dE = pl_dE;
+  ri.pl_alpha = pl_alpha;
+  const int e_base = rp->e_base;
+  rec_weights_block(sh, ri, e_base, A.b + off, A.S + off, A.lnP + off, A.lnW + off);
+  __syncthreads();   // all threads have read the record
   if (threadIdx.x == 0) {
-    rec_weights_seq(*rc, rp->e_base, A.b + off, A.S + off, A.lnP + off, A.lnW + off);
-    rp->e_bot = rp->e_base + 4 * rc->k_lo;
+    rc->profile = profile;
+    rc->pl_dE = pl_dE;
+    rc->pl_alpha = pl_alpha;
+    rp->e_bot = e_base + 4 * ri.k_lo;
     rp->e_top = 0;
   }
-  __syncthreads();
-  build_table_block(rp, A.lnW + off, rec_low(*rc), rc->k_top, tables);
+  build_table_block(rp, A.lnW + off, rec_low(ri), ri.k_top, tables);
 }
 
 // Seeded prior from caller-given steps: b(k) = src(k) on [k_seed, k_top) for realizations with
