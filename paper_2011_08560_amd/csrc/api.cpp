@@ -521,7 +521,7 @@ nfm_status nfm_get_spins(nfm_ctx* c, int64_t w0, int64_t count, int8_t* host_spi
 nfm_status nfm_compute_energies(nfm_ctx* c) {
   NFM_GUARD(c);
   if (!c->couplings) return fail(c, NFM_ESTATE, "compute_energies: couplings not set");
-  hipError_t e = nfm::launch_energy(c->d_reals(), c->n_real, max_walkers(c), c->d_jabi(), c->d_spins(),
+  hipError_t e = nfm::launch_energy(c->d_reals(), c->n_real, max_walkers(c), c->d_jk(), c->d_spins(),
                                     c->walker_state(), c->stream);
   if (e != hipSuccess) return fail(c, NFM_EDEVICE, std::string("energy: ") + hipGetErrorString(e));
   c->rt_reset = c->sweeps;

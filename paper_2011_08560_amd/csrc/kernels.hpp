@@ -23,7 +23,7 @@ hipError_t launch_pack_spins(const RealInfo* reals, int r, int wl0, int count, c
                              hipStream_t s);
 hipError_t launch_unpack_spins(const RealInfo* reals, int r, int wl0, int count, const uint32_t* spins, int8_t* dst,
                                hipStream_t s);
-hipError_t launch_energy(const RealInfo* reals, int n_real, int max_walkers, const uint32_t* jabi,
+hipError_t launch_energy(const RealInfo* reals, int n_real, int max_walkers, const uint32_t* jk,
                          const uint32_t* spins, WalkerState ws, hipStream_t s);
 hipError_t launch_reduce_real(const RealInfo* reals, int n_real, WalkerState ws, RealStatsDev* out, hipStream_t s);
 // walkers without a completed round trip in the last `window` sweeps (flags optional; count added)

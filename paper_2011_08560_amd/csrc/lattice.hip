@@ -1,6 +1,8 @@
 // Lattice, coupling and spin kernels of libnfm: disorder draw (Sec. II), the
 // ABI <-> kernel layout conversions, initial spins, the energy of Eq. (1) and
 // the per-realization reduction of walker statistics (Sec. III).
+#include <type_traits>
+
 #include "kernels.hpp"
 #include "philox.hpp"
 
@@ -16,12 +18,34 @@ __device__ __forceinline__ void site_pos(int L, int x, int y, int z, int* word, 
   *bit = p & 31;
 }
 
-__device__ __forceinline__ int abi_j(const uint32_t* jabi, int JW, int d, int i) {
-  return (jabi[d * JW + (i >> 5)] >> (i & 31)) & 1;  // 1 <=> J = -1
+// f(L as a constant) for the lattice sizes the kernels take; one switch per wave, so that row, field
+// and word positions inside are constants.
+template <class F>
+__device__ __forceinline__ void for_size(int L, F f) {
+  switch (L) {
+    case 2: f(std::integral_constant<int, 2>{}); break;
+    case 4: f(std::integral_constant<int, 4>{}); break;
+    case 6: f(std::integral_constant<int, 6>{}); break;
+    case 8: f(std::integral_constant<int, 8>{}); break;
+    case 10: f(std::integral_constant<int, 10>{}); break;
+    case 12: f(std::integral_constant<int, 12>{}); break;
+    default: break;
+  }
+}
+
+// The even-numbered bits of v, closed up to the low half.
+__device__ __forceinline__ uint32_t even_bits(uint32_t v) {
+  v &= 0x55555555u;
+  v = (v | (v >> 1)) & 0x33333333u;
+  v = (v | (v >> 2)) & 0x0F0F0F0Fu;
+  v = (v | (v >> 4)) & 0x00FF00FFu;
+  return (v | (v >> 8)) & 0x0000FFFFu;
 }
 
 // Sec. II: 3V couplings, each -1 with probability 1/2. Stream bit c = d*N + i is bit c%32 of
 // output[m & 3] of Philox counter (m >> 2, id, 0, TAG_J), m = c/32, key = disorder seed.
+// A word of a direction covers 32 consecutive stream bits, so it is cut from two stream words (one
+// generator call per bit took 24 us for 1024 realizations of L = 10).
 __global__ void k_gen_couplings(const RealInfo* __restrict__ reals, uint32_t* __restrict__ jabi_all,
                                 uint32_t key0, uint32_t key1) {
   const RealInfo ri = reals[blockIdx.x];
@@ -29,15 +53,18 @@ __global__ void k_gen_couplings(const RealInfo* __restrict__ reals, uint32_t* __
   uint32_t* jabi = jabi_all + ri.jabi_off;
   for (int t = threadIdx.x; t < 3 * JW; t += blockDim.x) {
     const int d = t / JW, w = t % JW;
-    uint32_t word = 0;
-    for (int b = 0; b < 32; ++b) {
-      const int i = w * 32 + b;
-      if (i >= ri.N) break;
-      const uint32_t c = (uint32_t)(d * ri.N + i);
-      const uint32_t m = c >> 5;
-      const u32x4 r = philox4x32_10(m >> 2, ri.real_id, 0u, kTagJ, key0, key1);
-      word |= ((r.v[m & 3] >> (c & 31)) & 1u) << b;
+    const uint32_t c = (uint32_t)(d * ri.N + w * 32), m = c >> 5;
+    const u32x4 r = philox4x32_10(m >> 2, ri.real_id, 0u, kTagJ, key0, key1);
+    uint32_t lo = r.v[0], hi = r.v[1];
+    if ((m & 3) == 1) lo = r.v[1], hi = r.v[2];
+    if ((m & 3) == 2) lo = r.v[2], hi = r.v[3];
+    if ((m & 3) == 3) {
+      lo = r.v[3];
+      hi = philox4x32_10((m >> 2) + 1u, ri.real_id, 0u, kTagJ, key0, key1).v[0];
     }
+    uint32_t word = __builtin_amdgcn_alignbit(hi, lo, c & 31u);
+    const int valid = ri.N - w * 32;
+    if (valid < 32) word &= (1u << valid) - 1u;
     jabi[t] = word;
   }
 }
@@ -47,41 +74,47 @@ __global__ void k_gen_couplings(const RealInfo* __restrict__ reals, uint32_t* __
 //   0 Jz(x,y,z)  1 Jz(x,y,z-1)  2 Jy(x,y,z)  3 Jy(x,y-1,z)
 //   4 Jx of the partner bond (phi=0: bond x--x+1 owned by x; phi=1: bond x-1--x owned by x-1)
 //   5 Jx of the other bond   (phi=0: bond x-1--x owned by x-1; phi=1: bond x--x+1 owned by x)
+// A row of L bits of the ABI layout gives a row of the kernel layout by taking its even or its odd
+// bits, so a word is put together row by row from words in LDS (bit by bit from device memory: 38 us
+// for 1024 realizations of L = 10).
 __global__ void k_pack_couplings(RealInfo* __restrict__ reals, const uint32_t* __restrict__ jabi_all,
                                  uint32_t* __restrict__ jk_all) {
   RealInfo* rp = reals + blockIdx.x;
-  const int L = rp->L, N = rp->N, F = field_bits(L), NWP = plane_words(L), H = L / 2;
+  const int N = rp->N;
   const int JW = abi_plane_words(N);
   const uint32_t* jabi = jabi_all + rp->jabi_off;
   uint32_t* jk = jk_all + rp->jk_off;
-  const int total = 2 * L * 6 * NWP;
-  for (int t = threadIdx.x; t < total; t += blockDim.x) {
-    const int w = t % NWP;
-    const int kind = (t / NWP) % 6;
-    const int cz = t / (6 * NWP);
-    const int c = cz / L, z = cz % L;
-    uint32_t word = 0;
-    for (int b = 0; b < 32; ++b) {
-      const int p = w * 32 + b;
-      const int y = p / F, j = p % F;
-      if (y >= L || j >= H) continue;
-      const int phi = (c + y + z) & 1;
-      const int x = 2 * j + phi;
-      const int xm = (x + L - 1) % L, ym = (y + L - 1) % L, zm = (z + L - 1) % L;
-      auto idx = [L](int xx, int yy, int zz) { return xx + L * yy + L * L * zz; };
-      int bit = 0;
-      switch (kind) {
-        case 0: bit = abi_j(jabi, JW, 2, idx(x, y, z)); break;
-        case 1: bit = abi_j(jabi, JW, 2, idx(x, y, zm)); break;
-        case 2: bit = abi_j(jabi, JW, 1, idx(x, y, z)); break;
-        case 3: bit = abi_j(jabi, JW, 1, idx(x, ym, z)); break;
-        case 4: bit = phi == 0 ? abi_j(jabi, JW, 0, idx(x, y, z)) : abi_j(jabi, JW, 0, idx(xm, y, z)); break;
-        default: bit = phi == 0 ? abi_j(jabi, JW, 0, idx(xm, y, z)) : abi_j(jabi, JW, 0, idx(x, y, z)); break;
+  constexpr int kWords = abi_plane_words(kMaxL * kMaxL * kMaxL);
+  __shared__ uint32_t s_j[3 * kWords + 1];   // (a row's second word may lie past the last direction)
+  for (int t = threadIdx.x; t < 3 * JW + 1; t += blockDim.x) s_j[t] = t < 3 * JW ? jabi[t] : 0u;
+  __syncthreads();
+  for_size(rp->L, [&](auto Lc) {
+    constexpr int L = decltype(Lc)::value, F = field_bits(L), NWP = plane_words(L), H = L / 2;
+    constexpr uint32_t RM = (1u << H) - 1u;
+    for (int t = threadIdx.x; t < 2 * L * 6 * NWP; t += blockDim.x) {
+      const int w = t % NWP;
+      const int kind = (t / NWP) % 6;
+      const int cz = t / (6 * NWP);
+      const int c = cz / L, z = cz % L;
+      const int d = kind < 2 ? 2 : kind < 4 ? 1 : 0;
+      const int zs = kind == 1 ? (z ? z - 1 : L - 1) : z;
+      uint32_t word = 0;
+      for (int y = w * 32 / F; y < L && y < (w + 1) * 32 / F; ++y) {
+        const int phi = (c + y + z) & 1;
+        const int ys = kind == 3 ? (y ? y - 1 : L - 1) : y;
+        const int off = L * (ys + L * zs);
+        const uint32_t* q = s_j + d * JW + (off >> 5);
+        const uint32_t row = __builtin_amdgcn_alignbit(q[1], q[0], off & 31);
+        // bonds along x: the partner's is owned by the even site, the other's by the odd one (of the
+        // pair before for phi = 0)
+        const int odd = kind < 4 ? phi : kind - 4;
+        uint32_t f = even_bits(row >> odd) & RM;
+        if (kind == 5 && phi == 0) f = ((f << 1) | (f >> (H - 1))) & RM;
+        word |= f << (y * F - w * 32);
       }
-      word |= (uint32_t)bit << b;
+      jk[t] = word;
     }
-    jk[t] = word;
-  }
+  });
   // n_minus over the 3N valid bits
   __shared__ int cnt;
   if (threadIdx.x == 0) cnt = 0;
@@ -89,7 +122,7 @@ __global__ void k_pack_couplings(RealInfo* __restrict__ reals, const uint32_t* _
   int local = 0;
   for (int t = threadIdx.x; t < 3 * JW; t += blockDim.x) {
     const int w = t % JW;
-    uint32_t v = jabi[t];
+    uint32_t v = s_j[t];
     const int valid = N - w * 32;
     if (valid < 32) v &= (1u << valid) - 1u;
     local += __popc(v);
@@ -105,24 +138,50 @@ __global__ void k_pack_couplings(RealInfo* __restrict__ reals, const uint32_t* _
 
 // Initial spins: bit i of walker w is bit i%32 of output[m & 3] of counter
 // (m >> 2, 0, id, (w << 8) | TAG_SPIN), m = i/32, key = walker seed; bit set <=> S = -1.
-__global__ void k_gen_spins(const RealInfo* __restrict__ reals, int32_t r0, int32_t nr,
-                            uint32_t* __restrict__ spins, uint32_t key0, uint32_t key1) {
+// Rows start at even bits, so the even and the odd bits of the stream hold the rows of either parity
+// closed up, H = L / 2 bits each; a word of the layout takes its rows from them by position. Bound by
+// the generator and the row moves, about 2000 vector instructions a walker at L = 10 (1024
+// realizations x 64 walkers: 470 us bit by bit, with a generator call and a read-modify-write each;
+// 8 us so).
+__global__ void __launch_bounds__(64) k_gen_spins(const RealInfo* __restrict__ reals, int32_t r0, int32_t nr,
+                                                  uint32_t* __restrict__ spins, uint32_t key0, uint32_t key1) {
   const int r = r0 + blockIdx.y;
   if (blockIdx.y >= (unsigned)nr) return;
   const RealInfo ri = reals[r];
   const int wl = blockIdx.x * blockDim.x + threadIdx.x;
   if (wl >= ri.walkers) return;
-  const int L = ri.L, WPW = walker_words(L);
   uint32_t* base = spins + ri.spin_off;
-  for (int k = 0; k < WPW; ++k) base[(int64_t)k * ri.walkers + wl] = 0;
-  for (int i = 0; i < ri.N; ++i) {
-    const uint32_t m = (uint32_t)i >> 5;
-    const u32x4 rr = philox4x32_10(m >> 2, 0u, ri.real_id, ((uint32_t)wl << 8) | kTagSpin, key0, key1);
-    const uint32_t bit = (rr.v[m & 3] >> (i & 31)) & 1u;
-    int word, b;
-    site_pos(L, i % L, (i / L) % L, i / (L * L), &word, &b);
-    base[(int64_t)word * ri.walkers + wl] |= bit << b;
-  }
+  for_size(ri.L, [&](auto Lc) {
+    constexpr int L = decltype(Lc)::value, N = L * L * L, F = field_bits(L), NWP = plane_words(L), H = L / 2;
+    constexpr int M = abi_plane_words(N), SW = (M + 1) / 2;
+    uint32_t par[2][SW];   // even and odd bits of the stream
+#pragma unroll
+    for (int m = 0; m < M; m += 4) {
+      const u32x4 rr = philox4x32_10((uint32_t)(m / 4), 0u, ri.real_id, ((uint32_t)wl << 8) | kTagSpin, key0, key1);
+#pragma unroll
+      for (int i = 0; i < 4; i += 2) {
+        if (m + i >= M) continue;
+        par[0][(m + i) / 2] = even_bits(rr.v[i]) | even_bits(rr.v[i + 1]) << 16;
+        par[1][(m + i) / 2] = even_bits(rr.v[i] >> 1) | even_bits(rr.v[i + 1] >> 1) << 16;
+      }
+    }
+#pragma unroll
+    for (int cz = 0; cz < 2 * L; ++cz) {
+#pragma unroll
+      for (int w = 0; w < NWP; ++w) {
+        uint32_t word = 0;
+#pragma unroll
+        for (int y = w * 32 / F; y < L && y < (w + 1) * 32 / F; ++y) {
+          const int z = cz % L, phi = (cz / L + y + z) & 1;
+          const int off = H * (y + L * z), q = off >> 5, sh = off & 31;
+          uint32_t row = par[phi][q] >> sh;
+          if (sh + H > 32) row |= par[phi][q + 1 < SW ? q + 1 : q] << ((32 - sh) & 31);
+          word |= (row & ((1u << H) - 1u)) << (y * F - w * 32);
+        }
+        base[(int64_t)(cz * NWP + w) * ri.walkers + wl] = word;
+      }
+    }
+  });
 }
 
 // int8 spins (walker-major, N each) <-> kernel layout for walkers [wl0, wl0+count) of realization r.
@@ -155,31 +214,89 @@ __global__ void k_unpack_spins(const RealInfo* __restrict__ reals, int32_t r, in
   }
 }
 
-// Eq. (1): E = -sum over sites and forward directions of J S_i S_{i+e_d}. Resets the walker's
-// bookkeeping (E_min = E, no round trips, no new minimum).
-__global__ void k_energy(const RealInfo* __restrict__ reals, const uint32_t* __restrict__ jabi_all,
-                         const uint32_t* __restrict__ spins, WalkerState ws) {
+// Field rows y + 1 (UP) or y - 1 of a plane-colour string (periodic).
+template <int L, bool UP>
+__device__ __forceinline__ void rows_beside(const uint32_t (&in)[plane_words(L)], uint32_t (&out)[plane_words(L)]) {
+  constexpr int NWP = plane_words(L), BITS = L * field_bits(L), S = UP ? field_bits(L) : BITS - field_bits(L);
+  // bit p of the result is bit (p + S) mod BITS
+#pragma unroll
+  for (int w = 0; w < NWP; ++w) {
+    uint32_t v = 0;
+#pragma unroll
+    for (int k = 0; k < NWP; ++k) {
+      // where input word k lands, taken once below and once above the string's end
+#pragma unroll
+      for (int turn = 0; turn < 2; ++turn) {
+        const int at = 32 * k - S + turn * BITS - 32 * w;
+        if (at > -32 && at < 32) v |= at >= 0 ? in[k] << (at & 31) : in[k] >> (-at & 31);
+      }
+    }
+    const int valid = BITS - 32 * w;
+    out[w] = valid < 32 ? v & ((1u << (valid & 31)) - 1u) : v;
+  }
+}
+
+// Eq. (1): E = -sum over sites and forward directions of J S_i S_{i+e_d} = -3N + 2 (unsatisfied
+// bonds). Every bond has one end of colour 0, so the six bonds of those sites are all bonds: per word
+// of the colour's strings six exclusive ors and bit counts (bit by bit with divisions for each
+// neighbour: 415 us for 65536 walkers of L = 10; 7 us so, bound by the latency of a wave's
+// reads of the spins). Resets the walker's bookkeeping (E_min = E, no round trips, no new minimum).
+__global__ void __launch_bounds__(64) k_energy(const RealInfo* __restrict__ reals, const uint32_t* __restrict__ jk_all,
+                                               const uint32_t* __restrict__ spins, WalkerState ws) {
   const RealInfo ri = reals[blockIdx.y];
   const int wl = blockIdx.x * blockDim.x + threadIdx.x;
   if (wl >= ri.walkers) return;
-  const int L = ri.L, N = ri.N, JW = abi_plane_words(N);
-  const uint32_t* jabi = jabi_all + ri.jabi_off;
+  const uint32_t* jk = jk_all + ri.jk_off;
   const uint32_t* base = spins + ri.spin_off;
-  auto spin_bit = [&](int x, int y, int z) {
-    int word, b;
-    site_pos(L, x, y, z, &word, &b);
-    return (int)((base[(int64_t)word * ri.walkers + wl] >> b) & 1u);
-  };
   int E = 0;
-  for (int i = 0; i < N; ++i) {
-    const int x = i % L, y = (i / L) % L, z = i / (L * L);
-    const int s = spin_bit(x, y, z);
-    const int nb[3] = {spin_bit((x + 1) % L, y, z), spin_bit(x, (y + 1) % L, z), spin_bit(x, y, (z + 1) % L)};
-    for (int d = 0; d < 3; ++d) {
-      // J S_i S_j = -1 (unsatisfied, energy +1) iff an odd number of the three bits is set
-      E += ((s ^ nb[d] ^ abi_j(jabi, JW, d, i)) & 1) ? 1 : -1;
+  for_size(ri.L, [&](auto Lc) {
+    constexpr int L = decltype(Lc)::value, F = field_bits(L), NWP = plane_words(L), H = L / 2;
+    constexpr uint32_t RM = (1u << H) - 1u;
+    auto plane = [&](int c, int z, uint32_t (&v)[NWP]) {
+#pragma unroll
+      for (int w = 0; w < NWP; ++w) v[w] = base[(int64_t)((c * L + z) * NWP + w) * ri.walkers + wl];
+    };
+    int u = 0;
+    uint32_t S[NWP], O[NWP], Ob[NWP], On[NWP];
+    plane(1, L - 1, Ob);
+    plane(1, 0, O);
+#pragma unroll
+    for (int z = 0; z < L; ++z) {
+      plane(0, z, S);
+      plane(1, (z + 1) % L, On);
+      uint32_t up[NWP], dn[NWP];
+      rows_beside<L, true>(O, up);
+      rows_beside<L, false>(O, dn);
+#pragma unroll
+      for (int w = 0; w < NWP; ++w) {
+        // rows of the word and those whose sites have phi = (y + z) & 1 = 0
+        uint32_t all = 0, even = 0;
+#pragma unroll
+        for (int y = w * 32 / F; y < L && y < (w + 1) * 32 / F; ++y) {
+          all |= RM << (y * F - w * 32);
+          if (((y + z) & 1) == 0) even |= RM << (y * F - w * 32);
+        }
+        uint32_t first = 0;   // the first and the last site of each row
+#pragma unroll
+        for (int y = w * 32 / F; y < L && y < (w + 1) * 32 / F; ++y) first |= 1u << (y * F - w * 32);
+        const uint32_t last = first << (H - 1);
+        // the other neighbour along x: of the pair before (phi = 0), of the pair after (phi = 1)
+        const uint32_t before = ((O[w] << 1) & all & ~first) | ((O[w] >> (H - 1)) & first);
+        const uint32_t after = ((O[w] >> 1) & all & ~last) | ((O[w] << (H - 1)) & last);
+        const uint32_t other = (before & even) | (after & ~even);
+        const uint32_t* J = jk + z * 6 * NWP + w;
+        u += __popc((S[w] ^ On[w] ^ J[0]) & all) + __popc((S[w] ^ Ob[w] ^ J[NWP]) & all) +
+             __popc((S[w] ^ up[w] ^ J[2 * NWP]) & all) + __popc((S[w] ^ dn[w] ^ J[3 * NWP]) & all) +
+             __popc((S[w] ^ O[w] ^ J[4 * NWP]) & all) + __popc((S[w] ^ other ^ J[5 * NWP]) & all);
+      }
+#pragma unroll
+      for (int w = 0; w < NWP; ++w) {
+        Ob[w] = O[w];
+        O[w] = On[w];
+      }
     }
-  }
+    E = -3 * L * L * L + 2 * u;
+  });
   const int64_t g = ri.walker_off + wl;
   ws.E[g] = E;
   ws.E_min[g] = E;
@@ -269,10 +386,10 @@ hipError_t launch_unpack_spins(const RealInfo* reals, int r, int wl0, int count,
   return hipGetLastError();
 }
 
-hipError_t launch_energy(const RealInfo* reals, int n_real, int max_walkers, const uint32_t* jabi,
+hipError_t launch_energy(const RealInfo* reals, int n_real, int max_walkers, const uint32_t* jk,
                          const uint32_t* spins, WalkerState ws, hipStream_t s) {
   dim3 grid((max_walkers + 63) / 64, n_real);
-  hipLaunchKernelGGL(k_energy, grid, dim3(64), 0, s, reals, jabi, spins, ws);
+  hipLaunchKernelGGL(k_energy, grid, dim3(64), 0, s, reals, jk, spins, ws);
   return hipGetLastError();
 }
 
