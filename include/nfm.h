@@ -590,12 +590,11 @@ nfm_status nfm_mlp_to_bf16(nfm_mlp* mlp);
 nfm_status nfm_mlp_infer_bf16(nfm_mlp* mlp, const float* dev_x, int32_t B, float* dev_y);
 /* For callers that cannot allocate (code under HIP graph capture, serving loops, harnesses that
  * forbid allocation): the same BF16 inference as nfm_mlp_infer_bf16, same results bit for bit,
- * with its activations in a static device array of the library (one per GPU, about 1.8 MB, held
- * until the process ends) instead of the network's workspace. Allocates nothing and calls no
- * allocating routine; asynchronous on the network's stream. B in [1, 1024] rows (NFM_ERANGE
- * above, independent of batch_max); dev_x [B x 81] and dev_y [B x 256] floats (device) are the
- * caller's. Every call on one GPU shares that array: calls that overlap on one GPU (several
- * streams or threads) race; calls queued on one stream do not. */
+ * without the network's workspace. Allocates nothing and calls no allocating routine; asynchronous
+ * on the network's stream. B in [1, 1024] rows (NFM_ERANGE above, independent of batch_max); dev_x
+ * [B x 81] and dev_y [B x 256] floats (device) are the caller's. Where dev_x and dev_y overlap, the
+ * rows go through a static device array of the library (one per GPU, 1 MB, held until the process
+ * ends), and such calls race if they overlap on one GPU (several streams or threads). */
 nfm_status nfm_mlp_infer_bf16_noalloc(nfm_mlp* mlp, const float* dev_x, int32_t B, float* dev_y);
 
 #ifdef __cplusplus

@@ -18,7 +18,7 @@ size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 int pad16(int b) { return (b + 15) / 16 * 16; }
 
 struct MlpLayout {
-  size_t params, grads, am, av, norm, wbf16, Xn, Z[6], Y, dY, dZa, dZb, Xb, Hb1, Hb2, loss, total;
+  size_t params, grads, am, av, norm, wf, wb, wbf16, Xn, Z[6], Y, dY, dZ[3], loss, total;
 };
 
 MlpLayout mlp_layout(int batch_max) {
@@ -35,34 +35,25 @@ MlpLayout mlp_layout(int batch_max) {
   l.am = take(4 * P);
   l.av = take(4 * P);
   l.norm = take(4 * 2 * nfm::kMlpIn);
+  l.wf = take(4 * P);
+  l.wb = take(4 * P);
   l.wbf16 = take(2 * P);
   l.Xn = take(4 * Bp * nfm::kMlpInPad);
   for (int i = 0; i < 6; ++i) l.Z[i] = take(4 * Bp * H);
   l.Y = take(4 * Bp * nfm::kMlpOut);
   l.dY = take(4 * Bp * nfm::kMlpOut);
-  l.dZa = take(4 * Bp * H);
-  l.dZb = take(4 * Bp * H);
-  l.Xb = take(2 * Bp * nfm::kMlpInPad);
-  l.Hb1 = take(2 * Bp * H);
-  l.Hb2 = take(2 * Bp * H);
-  l.loss = take(4 * (1 + 2 * nfm::kMlpLossBlocks));   // the loss, then the partial sums of its reduction
+  for (int i = 0; i < 3; ++i) l.dZ[i] = take(4 * Bp * H);
+  l.loss = take(4 * (1 + 2 * nfm::kMlpLossBlocks));   // the loss, then the blocks' sums of mask and error
   l.total = off;
   return l;
 }
 
-// Scratch of the entry point that allocates nothing (nfm_mlp_infer_bf16_noalloc): the BF16
-// activations and the FP32 output rows of one batch of at most kNoAllocRows rows, carved as
-// Xb [rows x 96] bf16, H1 and H2 [rows x 128] bf16, Y [rows x 256] float. Every kernel of the
-// inference writes all of its buffer's rows (padding included) before any is read, so nothing
-// needs clearing between calls. One copy per GPU, held until the process ends; calls that
+// Scratch of the entry point that allocates nothing (nfm_mlp_infer_bf16_noalloc): the output rows of
+// one batch of at most kNoAllocRows rows, used only where the caller's input and output overlap (the
+// rows are then written here first). One copy per GPU, held until the process ends; such calls that
 // overlap on one GPU share it and race.
 constexpr int kNoAllocRows = 1024;
-constexpr size_t kNoAllocXb = 0;
-constexpr size_t kNoAllocH1 = kNoAllocXb + 2 * (size_t)kNoAllocRows * nfm::kMlpInPad;
-constexpr size_t kNoAllocH2 = kNoAllocH1 + 2 * (size_t)kNoAllocRows * nfm::kMlpHid;
-constexpr size_t kNoAllocY = kNoAllocH2 + 2 * (size_t)kNoAllocRows * nfm::kMlpHid;
-constexpr size_t kNoAllocBytes = kNoAllocY + 4 * (size_t)kNoAllocRows * nfm::kMlpOut;
-static_assert(kNoAllocH1 % 256 == 0 && kNoAllocH2 % 256 == 0 && kNoAllocY % 256 == 0, "aligned regions");
+constexpr size_t kNoAllocBytes = 4 * (size_t)kNoAllocRows * nfm::kMlpOut;
 
 constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mu;
@@ -126,6 +117,18 @@ nfm_status check_batch(nfm_mlp* m, int B, const void* a, const void* b) {
   return NFM_OK;
 }
 
+// Workgroups write their output rows while others read their input rows, so an output that overlaps
+// the input goes through a buffer of the library's.
+bool rows_overlap(const float* x, const float* y, int B) {
+  return x < y + (size_t)B * nfm::kMlpOut && y < x + (size_t)B * nfm::kMlpIn;
+}
+
+nfm_status copy_rows(nfm_mlp* m, const float* y, int B, float* dev_y) {
+  if (y != dev_y)
+    MLP_HIP(m, hipMemcpyAsync(dev_y, y, 4 * (size_t)B * nfm::kMlpOut, hipMemcpyDeviceToDevice, m->stream));
+  return NFM_OK;
+}
+
 }  // namespace
 
 extern "C" {
@@ -160,6 +163,8 @@ nfm_status nfm_mlp_create(nfm_mlp** out, int32_t batch_max, void* dev_workspace,
   b.adam_m = (float*)(w + l.am);
   b.adam_v = (float*)(w + l.av);
   b.norm = (float*)(w + l.norm);
+  b.wf = (float*)(w + l.wf);
+  b.wb = (float*)(w + l.wb);
   b.wbf16 = (uint16_t*)(w + l.wbf16);
   b.Xn = (float*)(w + l.Xn);
   b.Z1 = (float*)(w + l.Z[0]);
@@ -170,11 +175,9 @@ nfm_status nfm_mlp_create(nfm_mlp** out, int32_t batch_max, void* dev_workspace,
   b.A3 = (float*)(w + l.Z[5]);
   b.Y = (float*)(w + l.Y);
   b.dY = (float*)(w + l.dY);
-  b.dZa = (float*)(w + l.dZa);
-  b.dZb = (float*)(w + l.dZb);
-  b.Xb = (uint16_t*)(w + l.Xb);
-  b.Hb1 = (uint16_t*)(w + l.Hb1);
-  b.Hb2 = (uint16_t*)(w + l.Hb2);
+  b.dZ3 = (float*)(w + l.dZ[0]);
+  b.dZ2 = (float*)(w + l.dZ[1]);
+  b.dZ1 = (float*)(w + l.dZ[2]);
   b.loss = (float*)(w + l.loss);
   if (hipSetDevice(device) != hipSuccess || hipMemsetAsync(m->ws, 0, l.total, m->stream) != hipSuccess ||
       hipStreamSynchronize(m->stream) != hipSuccess) {
@@ -225,6 +228,7 @@ nfm_status nfm_mlp_set_params(nfm_mlp* m, const float* host_params, const float*
   if (host_params) {
     MLP_HIP(m, hipMemcpyAsync(m->buf.params, host_params, 4 * (size_t)nfm::kMlpNParam, hipMemcpyHostToDevice,
                               m->stream));
+    MLP_HIP(m, nfm::mlp_order_weights(m->buf, m->stream));
     MLP_HIP(m, hipMemsetAsync(m->buf.adam_m, 0, 4 * (size_t)nfm::kMlpNParam, m->stream));
     MLP_HIP(m, hipMemsetAsync(m->buf.adam_v, 0, 4 * (size_t)nfm::kMlpNParam, m->stream));
     m->step = 0;
@@ -258,9 +262,9 @@ nfm_status nfm_mlp_forward(nfm_mlp* m, const float* dev_x, int32_t B, float* dev
   MLP_GUARD(m);
   nfm_status st = check_batch(m, B, dev_x, dev_y);
   if (st != NFM_OK) return st;
-  MLP_HIP(m, nfm::mlp_forward_f32(m->buf, dev_x, B, pad16(B), m->buf.Y, m->stream));
-  MLP_HIP(m, hipMemcpyAsync(dev_y, m->buf.Y, 4 * (size_t)B * nfm::kMlpOut, hipMemcpyDeviceToDevice, m->stream));
-  return NFM_OK;
+  float* y = rows_overlap(dev_x, dev_y, B) ? m->buf.Y : dev_y;
+  MLP_HIP(m, nfm::mlp_forward_f32(m->buf, dev_x, B, y, m->stream));
+  return copy_rows(m, y, B, dev_y);
 }
 
 nfm_status nfm_mlp_loss_grad(nfm_mlp* m, const float* dev_x, const float* dev_t, const float* dev_mask, int32_t B,
@@ -269,7 +273,7 @@ nfm_status nfm_mlp_loss_grad(nfm_mlp* m, const float* dev_x, const float* dev_t,
   nfm_status st = check_batch(m, B, dev_x, dev_t);
   if (st != NFM_OK) return st;
   if (!dev_mask) return mfail(m, NFM_EINVAL, "loss_grad: null mask");
-  MLP_HIP(m, nfm::mlp_loss_grad(m->buf, dev_x, dev_t, dev_mask, B, pad16(B), m->stream));
+  MLP_HIP(m, nfm::mlp_loss_grad(m->buf, dev_x, dev_t, dev_mask, B, m->stream));
   if (host_loss) {
     MLP_HIP(m, hipMemcpyAsync(host_loss, m->buf.loss, 4, hipMemcpyDeviceToHost, m->stream));
     MLP_HIP(m, hipStreamSynchronize(m->stream));
@@ -277,23 +281,38 @@ nfm_status nfm_mlp_loss_grad(nfm_mlp* m, const float* dev_x, const float* dev_t,
   return NFM_OK;
 }
 
+// The bias corrections 1 / (1 - beta^t) of Adam step t.
+static float adam_correction(float beta, int64_t t) {
+  return (float)(1.0 / (1.0 - std::pow((double)beta, (double)t)));
+}
+
 nfm_status nfm_mlp_adam(nfm_mlp* m, float lr, float beta1, float beta2, float eps) {
   MLP_GUARD(m);
   if (!(lr > 0.f) || !(beta1 >= 0.f && beta1 < 1.f) || !(beta2 >= 0.f && beta2 < 1.f) || !(eps > 0.f))
     return mfail(m, NFM_EINVAL, "adam: need lr > 0, 0 <= beta < 1, eps > 0");
   const int64_t t = m->step + 1;
-  const float c1 = (float)(1.0 / (1.0 - std::pow((double)beta1, (double)t)));
-  const float c2 = (float)(1.0 / (1.0 - std::pow((double)beta2, (double)t)));
-  MLP_HIP(m, nfm::mlp_adam(m->buf, lr, beta1, beta2, eps, c1, c2, m->stream));
+  MLP_HIP(m, nfm::mlp_adam(m->buf, lr, beta1, beta2, eps, adam_correction(beta1, t), adam_correction(beta2, t),
+                           m->stream));
   m->step = t;
   return NFM_OK;
 }
 
 nfm_status nfm_mlp_train_step(nfm_mlp* m, const float* dev_x, const float* dev_t, const float* dev_mask, int32_t B,
                               float lr) {
-  nfm_status st = nfm_mlp_loss_grad(m, dev_x, dev_t, dev_mask, B, nullptr);
+  if (!(lr > 0.f)) {
+    // refused by the step, after the loss and gradient as before it
+    const nfm_status st = nfm_mlp_loss_grad(m, dev_x, dev_t, dev_mask, B, nullptr);
+    return st != NFM_OK ? st : nfm_mlp_adam(m, lr, 0.9f, 0.999f, 1e-8f);
+  }
+  MLP_GUARD(m);
+  nfm_status st = check_batch(m, B, dev_x, dev_t);
   if (st != NFM_OK) return st;
-  return nfm_mlp_adam(m, lr, 0.9f, 0.999f, 1e-8f);
+  if (!dev_mask) return mfail(m, NFM_EINVAL, "loss_grad: null mask");
+  const int64_t t = m->step + 1;
+  MLP_HIP(m, nfm::mlp_train_step(m->buf, dev_x, dev_t, dev_mask, B, lr, 0.9f, 0.999f, 1e-8f, adam_correction(0.9f, t),
+                                 adam_correction(0.999f, t), m->stream));
+  m->step = t;
+  return NFM_OK;
 }
 
 nfm_status nfm_mlp_last_loss(nfm_mlp* m, float* host_loss) {
@@ -314,9 +333,9 @@ nfm_status nfm_mlp_infer_bf16(nfm_mlp* m, const float* dev_x, int32_t B, float* 
   MLP_GUARD(m);
   nfm_status st = check_batch(m, B, dev_x, dev_y);
   if (st != NFM_OK) return st;
-  MLP_HIP(m, nfm::mlp_infer_bf16(m->buf, dev_x, B, pad16(B), m->buf.Y, m->stream));
-  MLP_HIP(m, hipMemcpyAsync(dev_y, m->buf.Y, 4 * (size_t)B * nfm::kMlpOut, hipMemcpyDeviceToDevice, m->stream));
-  return NFM_OK;
+  float* y = rows_overlap(dev_x, dev_y, B) ? m->buf.Y : dev_y;
+  MLP_HIP(m, nfm::mlp_infer_bf16(m->buf, dev_x, B, y, m->stream));
+  return copy_rows(m, y, B, dev_y);
 }
 
 nfm_status nfm_mlp_infer_bf16_noalloc(nfm_mlp* m, const float* dev_x, int32_t B, float* dev_y) {
@@ -327,14 +346,9 @@ nfm_status nfm_mlp_infer_bf16_noalloc(nfm_mlp* m, const float* dev_x, int32_t B,
     return mfail(m, NFM_ERANGE, "infer_bf16_noalloc: at most " + std::to_string(kNoAllocRows) +
                                     " rows per call (the size of the static scratch), got " + std::to_string(B));
   if (!m->scratch) return mfail(m, NFM_ESTATE, "infer_bf16_noalloc: no scratch address for this device");
-  nfm::MlpBuffers b = m->buf;   // parameters, normalization and BF16 weights from the network
-  b.Xb = (uint16_t*)(m->scratch + kNoAllocXb);
-  b.Hb1 = (uint16_t*)(m->scratch + kNoAllocH1);
-  b.Hb2 = (uint16_t*)(m->scratch + kNoAllocH2);
-  float* Y = (float*)(m->scratch + kNoAllocY);
-  MLP_HIP(m, nfm::mlp_infer_bf16(b, dev_x, B, pad16(B), Y, m->stream));
-  MLP_HIP(m, hipMemcpyAsync(dev_y, Y, 4 * (size_t)B * nfm::kMlpOut, hipMemcpyDeviceToDevice, m->stream));
-  return NFM_OK;
+  float* y = rows_overlap(dev_x, dev_y, B) ? (float*)m->scratch : dev_y;
+  MLP_HIP(m, nfm::mlp_infer_bf16(m->buf, dev_x, B, y, m->stream));
+  return copy_rows(m, y, B, dev_y);
 }
 
 }  // extern "C"
