@@ -313,7 +313,9 @@ nfm_status nfm_wl_to_rec(nfm_ctx* ctx, int32_t profile, double pl_dE, double pl_
  *     hold a whole SIMD (their serial chains bound a sweep of the batch, and run fastest alone),
  *     beside a persistent queue over the remaining sizes on the SIMDs left free (at most half the
  *     SIMDs go to the largest size), launched on a second stream of the library's behind a short
- *     wait, forked from and joined to the context's stream; a batch of one size runs as 1. A
+ *     wait, forked from and joined to the context's stream; a batch of one size runs as 1, and
+ *     one of at most as many waves as SIMDs as 0 (nothing would queue), unless speculate,
+ *     waves_per_cu or hist is set. A
  *     persistent launch over sizes up to 8 or 10 uses the form compiled for them (fewer registers).
  *   waves_per_cu: persistent schedule only, resident workgroups per compute unit (0 = as many
  *     as fit).

@@ -656,6 +656,12 @@ static nfm_status muca_launches(nfm_ctx* c, uint64_t t0, uint64_t n_sweeps, int 
   // schedule 2 splits off the largest size (a batch of one size runs as the plain persistent queue)
   SplitPart big, rest;
   const bool split = schedule == 2 && plan_split(c, &big, &rest) && ensure_split_stream(c);
+  // A persistent launch of one size with at most one wave per SIMD has nothing to queue: it runs as the
+  // size's own launch, whose forms for waves alone are faster (48 waves of L = 6: 9.7 us per sweep
+  // beside generator waves, 13.1 in the queue; L = 8: 21.9 and 27.3). Not where the queue's own options
+  // are set.
+  const bool no_queue = c->group_L.size() == 1 && c->lay.total_waves <= 4LL * c->n_cu && speculate != 1 &&
+                        waves_per_cu == 0 && hist_mode == 0;
   uint64_t done = 0;
   while (done < n_sweeps) {
     const uint32_t chunk = (uint32_t)std::min<uint64_t>(per_launch, n_sweeps - done);
@@ -684,15 +690,16 @@ static nfm_status muca_launches(nfm_ctx* c, uint64_t t0, uint64_t n_sweeps, int 
       NFM_HIP(c, hipEventRecord(c->split_join, c->split_stream));
       NFM_HIP(c, hipStreamWaitEvent(c->stream, c->split_join, 0));
       nfm::note_partitioned_launch(spec);
-    } else if (schedule >= 1) {
+    } else if (schedule >= 1 && !no_queue) {
       const bool spec = speculate == 1;
       const int maxl = c->group_L.empty() ? nfm::kMaxL : c->group_L.back();
       int wpc = schedule == 1 ? waves_per_cu : 0;
       if (wpc <= 0) wpc = std::max(1, nfm::queue_blocks_per_cu(spec, lds_all, k_all, hist_mode, maxl));
       const int64_t grid = std::min<int64_t>(c->lay.total_waves, (int64_t)wpc * c->n_cu);
+      const bool alone = nfm::queue_alone(spec, lds_all, k_all, hist_mode, maxl, grid, c->n_cu);
       hipError_t e = nfm::launch_muca_queue(a, (const int32_t*)(c->ws + c->lay.order), (int)c->lay.total_waves,
                                             (uint32_t*)(c->ws + c->lay.counter), (int)grid, c->n_cu, lds_all, k_all,
-                                            hist_mode, spec, c->stream, maxl);
+                                            hist_mode, spec, c->stream, maxl, alone);
       if (e != hipSuccess) return fail(c, NFM_EDEVICE, std::string("muca_queue: ") + hipGetErrorString(e));
     } else {
       for (size_t g = 0; g < c->group_L.size(); ++g) {

@@ -86,6 +86,8 @@ hipError_t launch_muca_queue(SweepArgs a, const int32_t* order, int n_items, uin
                              bool solo = false);
 // resident workgroups per CU of the persistent kernel (0 on error)
 int queue_blocks_per_cu(bool spec, int lds_rows, int hist_levels, int hist_mode, int maxl, bool solo = false);
+// whether a persistent grid runs in the SIMD-exclusive form although it is not split
+bool queue_alone(bool spec, int lds_rows, int hist_levels, int hist_mode, int maxl, int64_t grid, int n_cu);
 // a short bounded wait on stream s (orders the placement of two launches on two streams)
 hipError_t launch_hold(hipStream_t s);
 hipError_t launch_pt_sweeps(int L, const SweepArgs& a, int n_waves, hipStream_t s);

@@ -88,7 +88,7 @@ static const void* queue_kernel(bool spec, int maxl, bool solo) {
 static HistPlan queue_plan(bool spec, int maxl, bool solo, int lds_rows, int hist_levels, int want_blocks,
                            int mode) {
   const int jl = solo ? kMaxL : queue_maxl(maxl);
-  const size_t staged = solo ? staged_bytes<kMaxL>() + 12 : 0;   // after the histogram, 16-byte aligned
+  const size_t staged = solo && maxl >= 12 ? staged_bytes<kMaxL>() + 12 : 0;   // after the histogram, 16-byte aligned
   return plan_hist(queue_kernel(spec, maxl, solo), (size_t)lds_rows * 32 + (size_t)jk_words(jl) * 4 + staged, lds_rows,
                    hist_levels, want_blocks, mode);
 }
@@ -99,6 +99,14 @@ int queue_blocks_per_cu(bool spec, int lds_rows, int hist_levels, int hist_mode,
   const HistPlan h = queue_plan(spec, maxl, solo, lds_rows, hist_levels, 1 << 20, hist_mode);
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k, 64, h.lds) != hipSuccess) return 0;
   return n;
+}
+
+// A grid of at most one workgroup per SIMD runs in the SIMD-exclusive form where that keeps all of it
+// resident: each wave has a SIMD to itself either way, and that form's generator is the one for
+// waves alone.
+bool queue_alone(bool spec, int lds_rows, int hist_levels, int hist_mode, int maxl, int64_t grid, int n_cu) {
+  return grid <= 4LL * n_cu &&
+         (int64_t)queue_blocks_per_cu(spec, lds_rows, hist_levels, hist_mode, maxl, true) * n_cu >= grid;
 }
 
 hipError_t launch_muca_queue(SweepArgs a, const int32_t* order, int n_items, uint32_t* counter, int grid, int n_cu,

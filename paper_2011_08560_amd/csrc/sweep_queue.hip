@@ -14,16 +14,20 @@ namespace nfm {
 // register file of its SIMD (all 256 accumulation registers besides its own), so no other wave
 // shares that SIMD's issue slots while it runs; for the largest lattices, whose serial chains
 // bound the batch.
+// The uniform rounds: a wave alone on its SIMD takes them on the vector unit, at L = 12 staged (89.5 us
+// per sweep against 93.6 on the scalar unit); beside others, and where speculation's second reads need
+// the registers, on the scalar unit.
+// (L = 6 planes are unrolled in the form for waves alone, 13.1 us per sweep against 13.7; beside other
+// sizes the code is too much for the instruction cache: five-size batch 92.8 us per sweep rolled, 94.4.)
+template <bool SPEC, bool SOLO>
+constexpr Gen queue_gen(int L) { return !SOLO || SPEC ? kGenScalar : L >= 12 ? kGenStaged : kGenVector; }
+
 template <bool SPEC, int MAXL, bool SOLO = false>
 __global__ void __launch_bounds__(64, MAXL <= 8 ? 3 : MAXL <= 10 ? 2 : 1) k_sweeps_queue(SweepArgs A, const int32_t* __restrict__ order, int n_items,
                                                      uint32_t* __restrict__ counter) {
   extern __shared__ uint32_t stab[];
   (void)stab;
   if constexpr (SOLO) asm volatile("" ::: "a255");
-  // A wave alone on its SIMD takes the uniform rounds staged (L = 12: 89.5 us per sweep against 93.6
-  // on the scalar unit); beside others, and where speculation's second reads need the registers, on
-  // the scalar unit.
-  constexpr Gen gen = SOLO && !SPEC ? kGenStaged : kGenScalar;
   for (;;) {
     __syncthreads();  // the previous item's table reads are done before the next table is loaded
     int item = 0;
@@ -34,12 +38,12 @@ __global__ void __launch_bounds__(64, MAXL <= 8 ? 3 : MAXL <= 10 ? 2 : 1) k_swee
     if (item >= n_items) break;
     const int wave = order[item];
     switch (A.reals[A.wave_real[wave]].L) {
-      case 2: sweep_wave<2, SPEC, false, false, gen, true>(A, wave); break;
-      case 4: if constexpr (MAXL >= 4) sweep_wave<4, SPEC, false, false, gen, true>(A, wave); break;
-      case 6: if constexpr (MAXL >= 6) sweep_wave<6, SPEC, false, false, gen, true>(A, wave); break;
-      case 8: if constexpr (MAXL >= 8) sweep_wave<8, SPEC, false, false, gen, true>(A, wave); break;
-      case 10: if constexpr (MAXL >= 10) sweep_wave<10, SPEC, false, false, gen, true>(A, wave); break;
-      case 12: if constexpr (MAXL >= 12) sweep_wave<12, SPEC, false, false, gen, true>(A, wave); break;
+      case 2: sweep_wave<2, SPEC, false, false, queue_gen<SPEC, SOLO>(2), true>(A, wave); break;
+      case 4: if constexpr (MAXL >= 4) sweep_wave<4, SPEC, false, false, queue_gen<SPEC, SOLO>(4), true>(A, wave); break;
+      case 6: if constexpr (MAXL >= 6) sweep_wave<6, SPEC, false, false, queue_gen<SPEC, SOLO>(6), !SOLO>(A, wave); break;
+      case 8: if constexpr (MAXL >= 8) sweep_wave<8, SPEC, false, false, queue_gen<SPEC, SOLO>(8), true>(A, wave); break;
+      case 10: if constexpr (MAXL >= 10) sweep_wave<10, SPEC, false, false, queue_gen<SPEC, SOLO>(10), true>(A, wave); break;
+      case 12: if constexpr (MAXL >= 12) sweep_wave<12, SPEC, false, false, queue_gen<SPEC, SOLO>(12), true>(A, wave); break;
       default: break;
     }
   }

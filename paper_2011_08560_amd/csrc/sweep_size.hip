@@ -28,7 +28,8 @@ __global__ void __launch_bounds__(128) k_sweeps_ws(SweepArgs A) {
 
 // The uniform rounds of a form: on the scalar unit for the compact and tempering forms (usually
 // several waves per SIMD, which leave it idle), except L = 6 tempering (unrolled planes, scalar
-// registers short). The expanded table usually means a wave alone on its SIMD: on the vector unit
+// registers short) and L = 2 tempering (a sweep is eight attempts and an exchange, bound by its
+// chain). The expanded table usually means a wave alone on its SIMD: on the vector unit
 // (L = 8: 125 cycles per step against 130 staged), but staged at L = 12, where the sweep's start is
 // a small part of it (118 against 124); so is the compact form there, whose tables leave the SIMDs
 // one wave each (127 cycles against 136 on the scalar unit).
@@ -36,7 +37,7 @@ template <int L, bool SPEC, bool PT, bool XT>
 constexpr Gen gen_of() {
   if (XT) return L >= 12 ? kGenStaged : kGenVector;
   if (L >= 12 && !SPEC && !PT) return kGenStaged;
-  return PT && L == 6 ? kGenVector : kGenScalar;
+  return PT && (L == 6 || L == 2) ? kGenVector : kGenScalar;
 }
 
 template <int L, bool SPEC, bool PT, bool XT>

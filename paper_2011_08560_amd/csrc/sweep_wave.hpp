@@ -168,17 +168,15 @@ struct Track {
   uint64_t t_first, t_last;
 };
 
+// (Selects throughout: in a replay some lane takes nearly every branch.)
 __device__ __forceinline__ void track_attempt(Track& tr, int B, uint64_t tau, int Bbot, int Btop) {
-  if (B >= Btop) {
-    if (tr.state == 2) {
-      tr.trips += 1;
-      tr.t_last = tau;
-    }
-    if (tr.state == 0) tr.t_first = tau;
-    tr.state = 1;
-  } else if (B <= Bbot && tr.state == 1) {
-    tr.state = 2;
-  }
+  const bool top = B >= Btop;
+  const bool trip = top & (tr.state == 2), first = top & (tr.state == 0);
+  const bool bottom = (B <= Bbot) & (tr.state == 1);
+  tr.trips += trip ? 1u : 0u;
+  tr.t_last = trip ? tau : tr.t_last;
+  tr.t_first = first ? tau : tr.t_first;
+  tr.state = top ? 1 : bottom ? 2 : tr.state;
 }
 
 // Round-trip bookkeeping on energies, applied once per sweep (parallel tempering: a
@@ -190,18 +188,15 @@ struct TrackE {
 };
 
 __device__ __forceinline__ void track_energy(TrackE& tr, int E, uint64_t tau, int e_bot, int e_top) {
-  if (E < tr.Emin) tr.Emin = E;
-  if (E < e_bot) tr.newmin = 1;
-  if (E >= e_top) {
-    if (tr.state == 2) {
-      tr.trips += 1;
-      tr.t_last = tau;
-    }
-    if (tr.state == 0) tr.t_first = tau;
-    tr.state = 1;
-  } else if (E <= e_bot && tr.state == 1) {
-    tr.state = 2;
-  }
+  tr.Emin = min(tr.Emin, E);
+  tr.newmin = E < e_bot ? 1 : tr.newmin;
+  const bool top = E >= e_top;
+  const bool trip = top & (tr.state == 2), first = top & (tr.state == 0);
+  const bool bottom = (E <= e_bot) & (tr.state == 1);
+  tr.trips += trip ? 1u : 0u;
+  tr.t_last = trip ? tau : tr.t_last;
+  tr.t_first = first ? tau : tr.t_first;
+  tr.state = top ? 1 : bottom ? 2 : tr.state;
 }
 
 __device__ __forceinline__ int lds_load_i32(uint32_t byte_addr) {
@@ -626,7 +621,7 @@ __device__ __forceinline__ void sweep_wave(const SweepArgs& A, int wave) {
     uint32_t m0[NWP], m1[NWP], m2[NWP];
 #pragma unroll
     for (int w = 0; w < NWP; ++w) {
-      const uint32_t Xo = ((O[w] >> 1) & mp) | ((O[w] << (G::H - 1)) & mpw) | ((O[w] << 1) & mm) |
+      const uint32_t Xo = G::H == 1 ? O[w] : ((O[w] >> 1) & mp) | ((O[w] << (G::H - 1)) & mpw) | ((O[w] << 1) & mm) |
                           ((O[w] >> (G::H - 1)) & mmw);
       const uint32_t Up = ZB > 1 ? __builtin_amdgcn_alignbit(O[w], O[w], G::PB & 31) : Zp[w];
       const uint32_t Dn = ZB > 1 ? __builtin_amdgcn_alignbit(O[w], O[w], (32 - G::PB) & 31) : Zm[w];
@@ -661,6 +656,15 @@ __device__ __forceinline__ void sweep_wave(const SweepArgs& A, int wave) {
   // nibble), and the low and high nibbles of each byte masked out.
   auto expand = [&](const uint32_t (&V)[NBLK], int w, uint32_t (&A)[8], uint32_t (&D)[8]) __attribute__((always_inline)) {
     const uint32_t m0 = V[3 * w], m1 = V[3 * w + 1], m2 = V[3 * w + 2];
+    if constexpr (Q == 2) {   // two sites, bits 0 and 1 (the bytes above them are not read)
+      const uint32_t v0 = (m0 & 1u) | ((m1 << 1) & 2u) | (m2 << 2);
+      const uint32_t v1 = ((m0 >> 1) & 1u) | (m1 & 2u) | ((m2 << 1) & ~3u);
+      D[0] = v0 << 5;
+      D[1] = v1 << 5;
+      A[0] = (v0 << 2) & 0x1Cu;
+      A[1] = (v1 << 2) & 0x1Cu;
+      return;
+    }
     const uint32_t P0 = (m0 & 0x55555555u) | ((m1 << 1) & 0xAAAAAAAAu);   // sites 2i: bits 2i, 2i+1
     const uint32_t P1 = ((m0 >> 1) & 0x55555555u) | (m1 & 0xAAAAAAAAu);   // sites 2i + 1
     const uint32_t W[4] = {((P0 << 1) & 0x77777777u) | ((m2 << 3) & 0x88888888u),    // sites 4i
@@ -1041,7 +1045,14 @@ __device__ __forceinline__ void sweep_wave(const SweepArgs& A, int wave) {
         const int d = (Eh - E) / 4;   // energies of one realization share their residue mod 4
         const uint32_t th = pt_swap_threshold(A.pt_q[(int64_t)r * kMaxReplicas + slot], d);
         const uint32_t set = pt_set;   // set index within the realization
-        const u32x4 rr = philox4x32_10((uint32_t)(slot >> 2), (uint32_t)t, real_id, (set << 8) | kTagSwap, key0, key1);
+        u32x4 rr;
+        if constexpr (GEN == kGenVector) {   // all round keys are in registers
+          PhiloxRun pe{(uint32_t)(slot >> 2), (uint32_t)t, real_id, (set << 8) | kTagSwap};
+          philox_rounds<0, 10>(pe, kv);
+          rr = u32x4{{pe.c0, pe.c1, pe.c2, pe.c3}};
+        } else {
+          rr = philox4x32_10((uint32_t)(slot >> 2), (uint32_t)t, real_id, (set << 8) | kTagSwap, key0, key1);
+        }
         const int k4 = slot & 3;
         const uint32_t rw = k4 == 0 ? rr.v[0] : k4 == 1 ? rr.v[1] : k4 == 2 ? rr.v[2] : rr.v[3];
         dec = min(rw, 0xFFFFFFFEu) < th ? 1 : 0;

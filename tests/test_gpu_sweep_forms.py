@@ -73,3 +73,27 @@ def test_table_windows_match_oracle(nfm, orc, tuning, rows):
                     assert ws[f][r * W + w] == wr[f][0], (f, L, w)
             assert np.array_equal(H[b.level_offset(r):b.level_offset(r) + K], Href), L
         b.close()
+
+
+@pytest.mark.parametrize("L", [2, 6, 12])
+def test_one_size_under_the_persistent_schedule(nfm, L):
+    """A batch of one size with at most one wave per SIMD has nothing to queue and runs as the size's
+    own launch, unless the queue's options are set; the results are the same in each form, and in the
+    queue of a grid with several waves per SIMD."""
+    print("one size, persistent schedule: L", L, flush=True)
+    out = []
+    for tuning, form in ((dict(schedule=1), f"k_sweeps_ws<{L}>"), (dict(schedule=2), f"k_sweeps_ws<{L}>"),
+                         (dict(schedule=1, ws=1), f"k_sweeps_xt<{L}>"), (dict(schedule=1, waves_per_cu=1), "k_sweeps_queue"),
+                         (dict(schedule=1, hist=1), "k_sweeps_queue"), (dict(schedule=1, speculate=1), "k_sweeps_queue_spec")):
+        b = nfm.Batch([L] * 3, [64, 128, 64], DSEED, WSEED, first_real_id=7)
+        b.set_tuning(sweeps_per_launch=3, **tuning)
+        b.init_couplings()
+        b.init_spins()
+        b.compute_energies()
+        b.rec_init(0)
+        b.run_sweeps(5)
+        assert b.last_kernel() == form, tuning
+        out.append((b.get_spins(0, b.n_walkers), b.read_walkers(), b.read_histograms()))
+        b.close()
+    for o in out[1:]:
+        assert np.array_equal(o[0], out[0][0]) and np.array_equal(o[1], out[0][1]) and np.array_equal(o[2], out[0][2])
