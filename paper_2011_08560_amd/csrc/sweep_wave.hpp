@@ -168,15 +168,29 @@ struct Track {
   uint64_t t_first, t_last;
 };
 
-// (Selects throughout: in a replay some lane takes nearly every branch.)
+// SELECTS: without branches, for L = 2, where in most replays some lane takes each branch (1.73 us per
+// sweep with branches, 1.58 without); beyond, a replay is for one lane or two, and the branches that no
+// lane takes are skipped (L = 8 x 4096 production of 500 sweeps: 37.6 ms with branches, 38.0 without).
+template <bool SELECTS>
 __device__ __forceinline__ void track_attempt(Track& tr, int B, uint64_t tau, int Bbot, int Btop) {
-  const bool top = B >= Btop;
-  const bool trip = top & (tr.state == 2), first = top & (tr.state == 0);
-  const bool bottom = (B <= Bbot) & (tr.state == 1);
-  tr.trips += trip ? 1u : 0u;
-  tr.t_last = trip ? tau : tr.t_last;
-  tr.t_first = first ? tau : tr.t_first;
-  tr.state = top ? 1 : bottom ? 2 : tr.state;
+  if constexpr (SELECTS) {
+    const bool top = B >= Btop;
+    const bool trip = top & (tr.state == 2), first = top & (tr.state == 0);
+    const bool bottom = (B <= Bbot) & (tr.state == 1);
+    tr.trips += trip ? 1u : 0u;
+    tr.t_last = trip ? tau : tr.t_last;
+    tr.t_first = first ? tau : tr.t_first;
+    tr.state = top ? 1 : bottom ? 2 : tr.state;
+  } else if (B >= Btop) {
+    if (tr.state == 2) {
+      tr.trips += 1;
+      tr.t_last = tau;
+    }
+    if (tr.state == 0) tr.t_first = tau;
+    tr.state = 1;
+  } else if (B <= Bbot && tr.state == 1) {
+    tr.state = 2;
+  }
 }
 
 // Round-trip bookkeeping on energies, applied once per sweep (parallel tempering: a
@@ -996,7 +1010,7 @@ __device__ __forceinline__ void sweep_wave(const SweepArgs& A, int wave) {
             if (bmin < win.lo || bmax > win.hi) {
 #pragma unroll
               for (int k = 0; k < cnt; ++k)
-                track_attempt(tr, Bq[k], tau_blk + (uint64_t)(4 * g0 + k), Bbot, Btop);
+                track_attempt<L == 2>(tr, Bq[k], tau_blk + (uint64_t)(4 * g0 + k), Bbot, Btop);
               win = make_window(tr.state, Bbot, Btop);
               fold_minimum();
             }
