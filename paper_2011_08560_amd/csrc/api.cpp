@@ -422,14 +422,9 @@ uint64_t nfm_sweep_counter(const nfm_ctx* c) { return c ? c->sweeps : 0; }
 static nfm_status after_couplings(nfm_ctx* c) {
   hipError_t e = nfm::launch_pack_couplings(c->d_reals(), c->n_real, c->d_jabi(), c->d_jk(), c->stream);
   if (e != hipSuccess) return fail(c, NFM_EDEVICE, std::string("pack_couplings: ") + hipGetErrorString(e));
-  nfm_status s = pull_reals(c);
-  if (s != NFM_OK) return s;
-  for (auto& r : c->reals) {  // tables refer to the old level set
-    r.row0 = 0;
-    r.rows = 0;
-  }
-  c->couplings = true;
-  return push_reals(c);
+  const nfm_status s = pull_reals(c);
+  if (s == NFM_OK) c->couplings = true;
+  return s;
 }
 
 nfm_status nfm_init_couplings(nfm_ctx* c) {
@@ -1035,12 +1030,10 @@ nfm_status nfm_rec_update(nfm_ctx* c, double f_tol, nfm_rec_info* host_info) {
   hipError_t e = nfm::launch_rec_update(c->d_reals(), c->d_recs(), c->n_real, c->rec_arrays(), c->walker_state(),
                                         c->d_hist(), c->d_tables(), f_tol, c->stream);
   if (e != hipSuccess) return fail(c, NFM_EDEVICE, std::string("rec_update: ") + hipGetErrorString(e));
-  nfm_status st = pull_reals(c);
-  if (st != NFM_OK || !host_info) return st;
   static_assert(sizeof(nfm_rec_info) == sizeof(nfm::RecInfo), "layout");
-  NFM_HIP(c, hipMemcpyAsync(host_info, c->d_recs(), sizeof(nfm_rec_info) * c->n_real, hipMemcpyDeviceToHost, c->stream));
-  NFM_HIP(c, hipStreamSynchronize(c->stream));
-  return NFM_OK;
+  if (host_info)
+    NFM_HIP(c, hipMemcpyAsync(host_info, c->d_recs(), sizeof(nfm_rec_info) * c->n_real, hipMemcpyDeviceToHost, c->stream));
+  return pull_reals(c);   // waits
 }
 
 nfm_status nfm_rec_production(nfm_ctx* c, int32_t profile, double pl_dE, double pl_alpha) {

@@ -133,6 +133,8 @@ __global__ void k_pack_couplings(RealInfo* __restrict__ reals, const uint32_t* _
     rp->n_minus = cnt;
     rp->e_base = -3 * N + 2 * (cnt & 1);
     rp->K = (3 * N - rp->e_base) / 4 + 1;
+    rp->row0 = 0;   // no table: an earlier one referred to the old level set
+    rp->rows = 0;
   }
 }
 
