@@ -6,12 +6,10 @@
 
 namespace nfm {
 
-// The sampling wave beside a generator wave. Its step is bound by the chain from one threshold read
-// to the next (115-125 cycles at every size with one read per attempt), so it reads the thresholds
-// of both outcomes ahead (the paired form), speculation asked for or not: 95 (L = 12) to 107 cycles
-// per step where each wave has a SIMD. With a pair of waves per SIMD the vector issue of both binds:
-// 116 at L = 4, 125 at L = 6.
-template <int L>
+// The sampling wave beside a generator wave. Where each wave has a SIMD, its step is bound by the chain
+// from one threshold read to the next (115-125 cycles at every size with one read per attempt), so it
+// reads the thresholds of both outcomes ahead (the paired form): 95 (L = 12) to 107 cycles per step.
+template <int L, bool PAIRED>
 __global__ void __launch_bounds__(128) k_sweeps_ws(SweepArgs A) {
   extern __shared__ uint32_t stab[];  // addressed from LDS address 0
   (void)stab;
@@ -20,7 +18,7 @@ __global__ void __launch_bounds__(128) k_sweeps_ws(SweepArgs A) {
   if (role == 0) {
     // the sampling wave's decisions form the critical chain: its instructions go first
     __builtin_amdgcn_s_setprio(3);
-    sweep_wave<L, false, false, true, kGenWave>(A, (int)blockIdx.x);
+    sweep_wave<L, false, false, true, kGenWave, (L >= 8), PAIRED>(A, (int)blockIdx.x);
   } else {
     generate_words<L>(A, (int)blockIdx.x);
   }
@@ -65,18 +63,18 @@ static hipError_t launch_LS(const SweepArgs& a, int n_waves, size_t lds_bytes, h
   return hipGetLastError();
 }
 
-template <int L>
+template <int L, bool PAIRED>
 static hipError_t launch_ws(const SweepArgs& a, int n_waves, size_t lds_bytes, bool spec, hipStream_t s) {
   static int checked = 0;
   if (!checked) {
     hipFuncAttributes attr;
-    hipError_t e = hipFuncGetAttributes(&attr, reinterpret_cast<const void*>(&k_sweeps_ws<L>));
+    hipError_t e = hipFuncGetAttributes(&attr, reinterpret_cast<const void*>(&k_sweeps_ws<L, PAIRED>));
     if (e != hipSuccess) return e;
     if (attr.sharedSizeBytes != 0) return hipErrorInvalidKernelFile;
     checked = 1;
   }
   note_kernel(spec ? "k_sweeps_ws_spec" : "k_sweeps_ws", L);
-  hipLaunchKernelGGL((k_sweeps_ws<L>), dim3(n_waves), dim3(128), lds_bytes, s, a);
+  hipLaunchKernelGGL((k_sweeps_ws<L, PAIRED>), dim3(n_waves), dim3(128), lds_bytes, s, a);
   return hipGetLastError();
 }
 
@@ -99,14 +97,19 @@ hipError_t launch_L(SweepArgs a, int n_waves, int lds_rows, int hist_levels, int
         hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, f, 64, h.lds) == hipSuccess && occ_x >= std::min(occ, want)) {
       if (ws_mode != 1) {
         const size_t lds_w = (size_t)ws_ring_base(hist_levels, jk_words(L), hist_levels) + 3 * (size_t)ws_slot_bytes<L>();
-        const void* fw = reinterpret_cast<const void*>(&k_sweeps_ws<L>);
+        const void* fw = reinterpret_cast<const void*>(&k_sweeps_ws<L, true>);
         int occ_w = 0;
         const bool fits = hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ_w, fw, 128, lds_w) == hipSuccess &&
                           occ_w >= want;
         if (ws_mode == 2 ? occ_w >= 1 : (fits && n_waves <= 4 * n_cu)) {
           a.hist_margin = hist_levels;
           a.hist_n = hist_levels;
-          return launch_ws<L>(a, n_waves, lds_w, spec, s);
+          // With more pairs of waves than half the SIMDs, two waves share a SIMD and its vector issue
+          // binds: L = 6 then reads once per attempt (121 cycles per step, 125 paired); L = 4,
+          // whose attempts have fewer other instructions, stays paired (116, 119 read once), and
+          // beyond L = 6 so many pairs do not fit in LDS.
+          if (!spec && L >= 6 && n_waves > 2 * n_cu) return launch_ws<L, false>(a, n_waves, lds_w, spec, s);
+          return launch_ws<L, true>(a, n_waves, lds_w, spec, s);
         }
       }
       if (!spec) {

@@ -449,7 +449,7 @@ __host__ __device__ inline uint32_t staged_base(uint32_t hbase, int hist_n) {
 // XT (multicanonical, no speculation): the table is expanded on chip to one row per level of
 // the realization (rows outside the stored range repeat its edge rows, as the clamp would), so
 // the row of a level is the level itself and the decision needs no clamp.
-template <int L, bool SPEC, bool PT, bool XT, Gen GEN, bool ROLL = (L >= 8)>
+template <int L, bool SPEC, bool PT, bool XT, Gen GEN, bool ROLL = (L >= 8), bool PAIRED = false>
 __device__ __forceinline__ void sweep_wave(const SweepArgs& A, int wave) {
   using G = Geo<L>;
   constexpr int NWP = G::NWP, Q = G::Q, N = G::N, H = G::H, FB = G::F, ZB = G::ZB, LB = G::LB, NG = G::NG;
@@ -458,7 +458,7 @@ __device__ __forceinline__ void sweep_wave(const SweepArgs& A, int wave) {
   constexpr int NBLK = 3 * NWP;
   constexpr bool kRolled = ROLL && LB > 2;
   constexpr int kZUnroll = kRolled ? 1 : LB;
-  constexpr bool PAIR = !PT && (SPEC || GEN == kGenWave);   // thresholds of both outcomes read ahead
+  constexpr bool PAIR = !PT && (SPEC || PAIRED);   // thresholds of both outcomes read ahead
   constexpr bool WS = GEN == kGenWave, SU = GEN == kGenScalar, PS = GEN == kGenStaged;
   static_assert(!(PT && SPEC), "the tempering row does not depend on the decision");
   static_assert(!(XT && PT), "the expanded table is for the multicanonical form");
