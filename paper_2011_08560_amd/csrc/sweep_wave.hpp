@@ -10,11 +10,11 @@
 // instruction takes 4.2 cycles of the SIMD (adds, ands, ors, xors of vector registers and right
 // shifts 2.3), whatever it does: the 32 x 32 -> 64 bit product costs no more than a compare. A wave
 // alone on its SIMD issues one instruction of any kind per 4.5 (4-byte encodings) or 5.5 cycles
-// (8-byte). So an attempt is written for its instruction count: 18.7 vector instructions at L = 8
+// (8-byte). So an attempt is written for its instruction count: 19.1 vector instructions at L = 8
 // (16 products and 18 xors for four random words, 6 for the decision, 1 for the running extremes,
-// the rest block preparation), 14.1 in the tempering form. Measured: L = 8 x 4096 realizations
-// 70.4 us per sweep (82 cycles per wave-attempt and SIMD; 84 us with per-site gathering products
-// and a plane index resolved by compares and selects), tempering L = 8 x 2048 30.5 us (71).
+// the rest block preparation), 14.4 in the tempering form. Measured, after per-site gathering products
+// and a plane index resolved by compares and selects: L = 8 x 4096 realizations 81.5 -> 72.5 us per
+// sweep (power-law rounds), tempering 70.9 -> 53.9 us.
 //
 // The sweep order is checkerboard: all sites of colour 0, then colour 1. The
 // neighbours of a site all have the other colour, so at the start of each
