@@ -363,6 +363,14 @@ nfm_status nfm_sync(nfm_ctx* ctx);
 /* Name of the sweep kernel form the last sweep launch on the calling host thread used, e.g.
  * "k_sweeps_ws<6>" (a report for benchmarks; "none" before any launch). */
 const char* nfm_last_kernel(const nfm_ctx* ctx);
+/* Every kernel of that launch, separated by "; ", each as "name<L> form GRIDxTHREADS LDS", e.g.
+ * "k_sweeps_ws<6> paired 48x128 27616": L the lattice size (persistent kernels: the largest one they
+ * are compiled for), form the compiled variant that the name leaves open, LDS the bytes of a
+ * workgroup. Forms: where the uniform half of the first generator rounds is computed ("vector",
+ * "scalar", "staged"); beside a generator wave, whether the thresholds of both outcomes are read
+ * ahead ("paired") or one ("single"); persistent kernels, whether each wave holds a whole SIMD
+ * ("exclusive") or not ("shared"). A report for tests and measurements. */
+const char* nfm_last_launch(const nfm_ctx* ctx);
 
 /* Checkpoint and resume (the sweep counter travels with the state, so a run resumed from a
  * checkpoint draws the same random words and gives the same spins, energies, histograms, round

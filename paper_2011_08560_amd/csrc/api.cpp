@@ -661,6 +661,7 @@ static nfm_status muca_launches(nfm_ctx* c, uint64_t t0, uint64_t n_sweeps, int 
   while (done < n_sweeps) {
     const uint32_t chunk = (uint32_t)std::min<uint64_t>(per_launch, n_sweeps - done);
     nfm::SweepArgs a = muca_args(c, t0 + done, chunk, trace_cap);
+    nfm::begin_launch();
     if (split) {
       const bool spec = speculate == 1;
       const int32_t* order = (const int32_t*)(c->ws + c->lay.order);
@@ -828,6 +829,8 @@ nfm_status nfm_trace_config(nfm_ctx* c, int64_t walker_begin, int64_t count, int
 }
 
 const char* nfm_last_kernel(const nfm_ctx* c) { return c ? nfm::last_sweep_kernel() : "none"; }
+
+const char* nfm_last_launch(const nfm_ctx* c) { return c ? nfm::last_sweep_launch() : "none"; }
 
 nfm_status nfm_sync(nfm_ctx* c) {
   NFM_GUARD(c);
@@ -1506,6 +1509,7 @@ nfm_status nfm_pt_run_sweeps(nfm_ctx* c, uint64_t n_sweeps) {
   uint64_t done = 0;
   while (done < n_sweeps) {
     const uint32_t chunk = (uint32_t)std::min<uint64_t>(c->sweeps_per_launch, n_sweeps - done);
+    nfm::begin_launch();
     for (size_t g = 0; g < c->group_L.size(); ++g) {
       nfm::SweepArgs a{};
       a.reals = c->d_reals();

@@ -93,8 +93,11 @@ hipError_t launch_hold(hipStream_t s);
 hipError_t launch_pt_sweeps(int L, const SweepArgs& a, int n_waves, hipStream_t s);
 // the exchange thresholds of realization r as the sweep kernel computes them (inspection)
 hipError_t launch_pt_swap_table(const double* q, int r, int M, int D, uint32_t* swap, hipStream_t s);
-// name of the sweep kernel the last launch on this host thread used
+// name of the sweep kernel the last launch on this host thread used; every kernel of that launch
 const char* last_sweep_kernel();
+const char* last_sweep_launch();
+// starts the record of a launch (its kernels add to it)
+void begin_launch();
 // record a split persistent launch (the largest lattices in the SIMD-exclusive form beside the
 // others) as the last launch
 void note_partitioned_launch(bool spec);

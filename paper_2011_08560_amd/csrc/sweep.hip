@@ -3,6 +3,7 @@
 // sweep_queue.hip.
 #include <algorithm>
 #include <cstdio>
+#include <cstring>
 
 #include "sweep_launch.hpp"
 #include "sweep_wave.hpp"
@@ -33,13 +34,22 @@ hipError_t launch_fill_u32(uint32_t* p, int n, uint32_t v, hipStream_t s) {
   return hipGetLastError();
 }
 
-// Name of the sweep kernel the last launch on this host thread used (for reports).
+// The sweep kernels the last launch on this host thread used (for reports): the last one's name, and
+// every kernel of the launch with its compiled form, grid and LDS.
 static thread_local char g_last_kernel[48] = "none";
+static thread_local char g_last_launch[512] = "none";
 const char* last_sweep_kernel() { return g_last_kernel; }
-void note_kernel(const char* form, int L) { snprintf(g_last_kernel, sizeof(g_last_kernel), "%s<%d>", form, L); }
-void note_kernel_form(const char* form) { snprintf(g_last_kernel, sizeof(g_last_kernel), "%s", form); }
+const char* last_sweep_launch() { return g_last_launch; }
+void begin_launch() { g_last_launch[0] = '\0'; }
+void note_kernel(const char* kernel, int L, const char* form, int grid, int threads, size_t lds_bytes) {
+  const bool queue = strncmp(kernel, "k_sweeps_queue", 14) == 0;   // over several sizes: named without one
+  snprintf(g_last_kernel, sizeof(g_last_kernel), queue ? "%s" : "%s<%d>", kernel, L);
+  const size_t n = strlen(g_last_launch);
+  snprintf(g_last_launch + n, sizeof(g_last_launch) - n, "%s%s<%d> %s %dx%d %zu", n ? "; " : "", kernel, L, form, grid,
+           threads, lds_bytes);
+}
 void note_partitioned_launch(bool spec) {
-  note_kernel_form(spec ? "k_sweeps_queue_spec_solo" : "k_sweeps_queue_solo");
+  snprintf(g_last_kernel, sizeof(g_last_kernel), "%s", spec ? "k_sweeps_queue_spec_solo" : "k_sweeps_queue_solo");
 }
 
 // Levels kept on chip below the table rows and above them when the histogram is a window.

@@ -14,9 +14,9 @@ struct HistPlan {
 
 HistPlan plan_hist(const void* f, size_t base_lds, int rows, int K, int want_blocks, int mode);
 
-// Record the kernel form of the calling host thread's last sweep launch (for reports).
-void note_kernel(const char* form, int L);    // "form<L>"
-void note_kernel_form(const char* form);
+// Record a kernel of the calling host thread's last sweep launch (for reports): its name, lattice size
+// (persistent kernels: the largest they are compiled for), compiled form, grid and dynamic LDS.
+void note_kernel(const char* kernel, int L, const char* form, int grid, int threads, size_t lds_bytes);
 
 // Kernels of one lattice size (sweep_size.hip, compiled once per size).
 // ws_mode (expanded-table launches): 0 automatic -- the generator wave when the launch has at

@@ -72,7 +72,7 @@ static hipError_t launch_queue_S(const SweepArgs& a, const int32_t* order, int n
   }
   hipError_t e = launch_fill_u32(counter, 1, 0u, s);
   if (e != hipSuccess) return e;
-  note_kernel_form(SPEC ? "k_sweeps_queue_spec" : "k_sweeps_queue");
+  note_kernel(SPEC ? "k_sweeps_queue_spec" : "k_sweeps_queue", MAXL, SOLO ? "exclusive" : "shared", grid, 64, lds_bytes);
   hipLaunchKernelGGL((k_sweeps_queue<SPEC, MAXL, SOLO>), dim3(grid), dim3(64), lds_bytes, s, a, order, n_items,
                      counter);
   return hipGetLastError();

@@ -58,7 +58,9 @@ static hipError_t launch_LS(const SweepArgs& a, int n_waves, size_t lds_bytes, h
     if (attr.sharedSizeBytes != 0) return hipErrorInvalidKernelFile;
     checked = 1;
   }
-  note_kernel(PT ? "k_sweeps_pt" : SPEC ? "k_sweeps_spec" : XT ? "k_sweeps_xt" : "k_sweeps", L);
+  constexpr Gen gen = gen_of<L, SPEC, PT, XT>();
+  note_kernel(PT ? "k_sweeps_pt" : SPEC ? "k_sweeps_spec" : XT ? "k_sweeps_xt" : "k_sweeps", L,
+              gen == kGenStaged ? "staged" : gen == kGenScalar ? "scalar" : "vector", n_waves, 64, lds_bytes);
   hipLaunchKernelGGL((k_sweeps<L, SPEC, PT, XT>), dim3(n_waves), dim3(64), lds_bytes, s, a);
   return hipGetLastError();
 }
@@ -73,7 +75,7 @@ static hipError_t launch_ws(const SweepArgs& a, int n_waves, size_t lds_bytes, b
     if (attr.sharedSizeBytes != 0) return hipErrorInvalidKernelFile;
     checked = 1;
   }
-  note_kernel(spec ? "k_sweeps_ws_spec" : "k_sweeps_ws", L);
+  note_kernel(spec ? "k_sweeps_ws_spec" : "k_sweeps_ws", L, PAIRED ? "paired" : "single", n_waves, 128, lds_bytes);
   hipLaunchKernelGGL((k_sweeps_ws<L, PAIRED>), dim3(n_waves), dim3(128), lds_bytes, s, a);
   return hipGetLastError();
 }

@@ -137,6 +137,7 @@ def lib():
         "nfm_sync": (i32, [vp]),
         "nfm_checkpoint_bytes": (i32, [vp, C.POINTER(sz)]),
         "nfm_last_kernel": (C.c_char_p, [vp]),
+        "nfm_last_launch": (C.c_char_p, [vp]),
         "nfm_checkpoint": (i32, [vp, vp, sz]),
         "nfm_restore": (i32, [vp, vp, sz]),
         "nfm_set_histograms": (i32, [vp, vp]),
@@ -457,6 +458,16 @@ class Batch:
     def last_kernel(self) -> str:
         """The sweep kernel form the last launch used (nfm_last_kernel)."""
         return self._lib.nfm_last_kernel(self.ctx).decode()
+
+    def last_launch(self) -> list:
+        """(kernel, form, workgroups, threads, LDS bytes) of every kernel of the last launch (nfm_last_launch)."""
+        out = []
+        for part in self._lib.nfm_last_launch(self.ctx).decode().split("; "):
+            if part not in ("", "none"):
+                kernel, form, size, lds = part.split()
+                grid, threads = size.split("x")
+                out.append((kernel, form, int(grid), int(threads), int(lds)))
+        return out
 
     def checkpoint(self) -> np.ndarray:
         """The whole state of the context as a host byte array (nfm_checkpoint)."""
