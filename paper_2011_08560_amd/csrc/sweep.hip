@@ -98,7 +98,7 @@ static const void* queue_kernel(bool spec, int maxl, bool solo) {
 static HistPlan queue_plan(bool spec, int maxl, bool solo, int lds_rows, int hist_levels, int want_blocks,
                            int mode) {
   const int jl = solo ? kMaxL : queue_maxl(maxl);
-  const size_t staged = solo && maxl >= 12 ? staged_bytes<kMaxL>() + 12 : 0;   // after the histogram, 16-byte aligned
+  const size_t staged = solo && maxl >= 12 && !spec ? staged_bytes<kMaxL>() + 12 : 0;   // after the histogram, 16-byte aligned
   return plan_hist(queue_kernel(spec, maxl, solo), (size_t)lds_rows * 32 + (size_t)jk_words(jl) * 4 + staged, lds_rows,
                    hist_levels, want_blocks, mode);
 }

@@ -88,7 +88,7 @@ hipError_t launch_L(SweepArgs a, int n_waves, int lds_rows, int hist_levels, int
   const void* f = spec ? reinterpret_cast<const void*>(&k_sweeps<L, true, false, false>)
                        : reinterpret_cast<const void*>(&k_sweeps<L, false, false, false>);
   const int want = (n_waves + n_cu - 1) / std::max(n_cu, 1);
-  const size_t staged = L >= 12 ? staged_bytes<L>() + 12 : 0;   // after the histogram, 16-byte aligned
+  const size_t staged = L >= 12 && !spec ? staged_bytes<L>() + 12 : 0;   // after the histogram, 16-byte aligned
   const HistPlan h = plan_hist(f, (size_t)lds_rows * 32 + jb + staged, lds_rows, hist_levels, want, hist_mode);   // table, couplings
   if (hist_mode == 0) {
     // the expanded table (and every level of the histogram) when it costs no resident workgroups
