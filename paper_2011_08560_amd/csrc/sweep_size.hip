@@ -29,39 +29,37 @@ __global__ void __launch_bounds__(128) k_sweeps_ws(SweepArgs A) {
 // registers short) and L = 2 tempering (a sweep is eight attempts and an exchange, bound by its
 // chain). The expanded table usually means a wave alone on its SIMD: on the vector unit
 // (L = 8: 125 cycles per step against 130 staged), but staged at L = 12, where the sweep's start is
-// a small part of it (118 against 124); so is the compact form there, whose tables leave the SIMDs
-// one wave each (127 cycles against 136 on the scalar unit).
+// a small part of it (118 against 124). The compact form of L = 12 comes on the vector unit and
+// staged (launch_L chooses).
 template <int L, bool SPEC, bool PT, bool XT>
 constexpr Gen gen_of() {
   if (XT) return L >= 12 ? kGenStaged : kGenVector;
-  if (L >= 12 && !SPEC && !PT) return kGenStaged;
+  if (L >= 12 && !SPEC && !PT) return kGenVector;
   return PT && (L == 6 || L == 2) ? kGenVector : kGenScalar;
 }
 
-template <int L, bool SPEC, bool PT, bool XT>
+template <int L, bool SPEC, bool PT, bool XT, Gen GEN>
 __global__ void __launch_bounds__(64) k_sweeps(SweepArgs A) {
   extern __shared__ uint32_t stab[];  // addressed from LDS address 0 by sweep_wave
   (void)stab;
-  constexpr Gen gen = gen_of<L, SPEC, PT, XT>();
-  sweep_wave<L, SPEC, PT, XT, gen>(A, (int)blockIdx.x);
+  sweep_wave<L, SPEC, PT, XT, GEN>(A, (int)blockIdx.x);
 }
 
-template <int L, bool SPEC, bool PT, bool XT = false>
+template <int L, bool SPEC, bool PT, bool XT = false, Gen GEN = gen_of<L, SPEC, PT, XT>()>
 static hipError_t launch_LS(const SweepArgs& a, int n_waves, size_t lds_bytes, hipStream_t s) {
   // The kernel addresses its dynamic LDS block from address 0, which is only valid
   // when the compiler placed nothing else in LDS.
   static int checked = 0;
   if (!checked) {
     hipFuncAttributes attr;
-    hipError_t e = hipFuncGetAttributes(&attr, reinterpret_cast<const void*>(&k_sweeps<L, SPEC, PT, XT>));
+    hipError_t e = hipFuncGetAttributes(&attr, reinterpret_cast<const void*>(&k_sweeps<L, SPEC, PT, XT, GEN>));
     if (e != hipSuccess) return e;
     if (attr.sharedSizeBytes != 0) return hipErrorInvalidKernelFile;
     checked = 1;
   }
-  constexpr Gen gen = gen_of<L, SPEC, PT, XT>();
   note_kernel(PT ? "k_sweeps_pt" : SPEC ? "k_sweeps_spec" : XT ? "k_sweeps_xt" : "k_sweeps", L,
-              gen == kGenStaged ? "staged" : gen == kGenScalar ? "scalar" : "vector", n_waves, 64, lds_bytes);
-  hipLaunchKernelGGL((k_sweeps<L, SPEC, PT, XT>), dim3(n_waves), dim3(64), lds_bytes, s, a);
+              GEN == kGenStaged ? "staged" : GEN == kGenScalar ? "scalar" : "vector", n_waves, 64, lds_bytes);
+  hipLaunchKernelGGL((k_sweeps<L, SPEC, PT, XT, GEN>), dim3(n_waves), dim3(64), lds_bytes, s, a);
   return hipGetLastError();
 }
 
@@ -85,14 +83,13 @@ hipError_t launch_L(SweepArgs a, int n_waves, int lds_rows, int hist_levels, int
                            int ws_mode, bool spec, bool pt, hipStream_t s) {
   const size_t jb = (size_t)jk_words(L) * 4;
   if (pt) return launch_LS<L, false, true>(a, n_waves, (size_t)a.pt_M * 32 + 3 * 256 + jb, s);
-  const void* f = spec ? reinterpret_cast<const void*>(&k_sweeps<L, true, false, false>)
-                       : reinterpret_cast<const void*>(&k_sweeps<L, false, false, false>);
+  const void* f = spec ? reinterpret_cast<const void*>(&k_sweeps<L, true, false, false, gen_of<L, true, false, false>()>)
+                       : reinterpret_cast<const void*>(&k_sweeps<L, false, false, false, gen_of<L, false, false, false>()>);
   const int want = (n_waves + n_cu - 1) / std::max(n_cu, 1);
-  const size_t staged = L >= 12 && !spec ? staged_bytes<L>() + 12 : 0;   // after the histogram, 16-byte aligned
-  const HistPlan h = plan_hist(f, (size_t)lds_rows * 32 + jb + staged, lds_rows, hist_levels, want, hist_mode);   // table, couplings
+  const HistPlan h = plan_hist(f, (size_t)lds_rows * 32 + jb, lds_rows, hist_levels, want, hist_mode);   // table, couplings
   if (hist_mode == 0) {
     // the expanded table (and every level of the histogram) when it costs no resident workgroups
-    const void* fx = reinterpret_cast<const void*>(&k_sweeps<L, false, false, true>);
+    const void* fx = reinterpret_cast<const void*>(&k_sweeps<L, false, false, true, gen_of<L, false, false, true>()>);
     const size_t lds_x = staged_base((uint32_t)((size_t)hist_levels * 32 + jb), hist_levels) + (L >= 12 ? staged_bytes<L>() : 0);
     int occ_x = 0, occ = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ_x, fx, 64, lds_x) == hipSuccess &&
@@ -118,6 +115,25 @@ hipError_t launch_L(SweepArgs a, int n_waves, int lds_rows, int hist_levels, int
         a.hist_margin = hist_levels;
         a.hist_n = hist_levels;
         return launch_LS<L, false, false, true>(a, n_waves, lds_x, s);
+      }
+    }
+  }
+  if constexpr (L >= 12) {
+    // Staged words take 6.9 KB of LDS: only where several waves share a SIMD (its issue slots, not a
+    // wave's chain, bind) and no resident workgroup is lost. 1300 waves, tables of 400 rows: 127.6 us
+    // per sweep staged, 133.4 on the vector unit; 600 rows (5 per compute unit staged, 6 not): 176.7,
+    // 135.0. Waves alone: 1024 waves, 677 rows 92.6 staged, 90.7 on the vector unit.
+    if (!spec) {
+      const void* fs = reinterpret_cast<const void*>(&k_sweeps<L, false, false, false, kGenStaged>);
+      const size_t words = staged_bytes<L>() + 12;   // after the histogram, 16-byte aligned
+      const HistPlan hs = plan_hist(fs, (size_t)lds_rows * 32 + jb + words, lds_rows, hist_levels, want, hist_mode);
+      int occ_s = 0, occ = 0;
+      if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ_s, fs, 64, hs.lds) == hipSuccess &&
+          hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, f, 64, h.lds) == hipSuccess &&
+          std::min(occ, want) > 4 && occ_s >= std::min(occ, want)) {
+        a.hist_margin = hs.margin;
+        a.hist_n = hs.n;
+        return launch_LS<L, false, false, false, kGenStaged>(a, n_waves, hs.lds, s);
       }
     }
   }

@@ -55,3 +55,31 @@ def test_speculative_forms_hold_no_staged_words(nfm, schedule):
     rows = max(len(b.get_thresholds(0)[0]), 1)
     assert launch[0][4] == _plain(b, rows)
     b.close()
+
+
+# (waves per compute unit, rows): waves alone; SIMDs shared with room for staged words; without room
+# (as many workgroups as fit 160 KB without the words, or fewer)
+@pytest.mark.parametrize("per_cu,rows,form", [(4, 720, "vector"), (5, 720, "vector"), (6, 660, "vector"),
+                                              (5, 60, "staged"), (7, 200, "staged"), (8, 400, "vector")])
+def test_staged_words_cost_no_resident_workgroup(nfm, orc, per_cu, rows, form):
+    import torch
+    n_cu = torch.cuda.get_device_properties(0).multi_processor_count
+    n, T = (per_cu - 1) * n_cu + 40, 2
+    print("L = 12:", n, "waves,", rows, "rows", flush=True)
+    b = _batch(nfm, [L] * n, rows, schedule=0)
+    table_rows = max(len(b.get_thresholds(r)[0]) for r in range(n))
+    b.run_sweeps(T)
+    (kernel, got, grid, threads, lds), = b.last_launch()
+    assert (kernel, got, grid, threads) == ("k_sweeps<12>", form, n, 64)
+    fit = LDS_PER_CU // _plain(b, table_rows)
+    assert LDS_PER_CU // lds >= min(fit, per_cu)
+    # the last realization against the oracle
+    r = n - 1
+    thr, row0 = b.get_thresholds(r)
+    w0, off = b.walker_offset(r), b.level_offset(r)
+    rz = orc.make_realization(L, DSEED, r, WSEED, 64)
+    Hr, _ = orc.sample(rz, thr, row0, 0, 0, T)
+    assert np.array_equal(b.read_histograms()[off:off + rz.K], Hr)
+    assert np.array_equal(b.get_spins(w0, 64).reshape(64, -1), rz.S)
+    assert np.array_equal(b.read_walkers()["E"][w0:w0 + 64], rz.w["E"])
+    b.close()
