@@ -315,8 +315,10 @@ nfm_status nfm_wl_to_rec(nfm_ctx* ctx, int32_t profile, double pl_dE, double pl_
  *     SIMDs go to the largest size), launched on a second stream of the library's behind a short
  *     wait, forked from and joined to the context's stream; a batch of one size runs as 1, and
  *     one of at most as many waves as SIMDs as 0 (nothing would queue), unless speculate,
- *     waves_per_cu or hist is set. A
- *     persistent launch over sizes up to 8 or 10 uses the form compiled for them (fewer registers).
+ *     waves_per_cu or hist is set. A persistent launch over sizes up to 8 or 10 uses the kernels
+ *     compiled for them (fewer registers), and one of at most as many workgroups as SIMDs those for
+ *     waves alone, which leave half of each SIMD's registers to kernels of other streams; only the
+ *     largest size's part of the split leaves none on its SIMDs.
  *   waves_per_cu: persistent schedule only, resident workgroups per compute unit (0 = as many
  *     as fit).
  *   hist: extent of a launch's on-chip histogram. 0 automatic: every level of the realization
@@ -368,8 +370,8 @@ const char* nfm_last_kernel(const nfm_ctx* ctx);
  * are compiled for), form the compiled variant that the name leaves open, LDS the bytes of a
  * workgroup. Forms: where the uniform half of the first generator rounds is computed ("vector",
  * "scalar", "staged"); beside a generator wave, whether the thresholds of both outcomes are read
- * ahead ("paired") or one ("single"); persistent kernels, whether each wave holds a whole SIMD
- * ("exclusive") or not ("shared"). A report for tests and measurements. */
+ * ahead ("paired") or one ("single"); persistent kernels: several waves per SIMD ("shared"), at most
+ * one ("lone"), one that holds the whole SIMD ("exclusive"). A report for tests and measurements. */
 const char* nfm_last_launch(const nfm_ctx* ctx);
 
 /* Checkpoint and resume (the sweep counter travels with the state, so a run resumed from a

@@ -15,8 +15,8 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "libnfm.so")
 BUILD = os.path.join(HERE, "_build")
-# (source, object, definitions): the sweep kernels compile per lattice size and per queue form
-SOURCES = ([("sweep_queue.hip", f"sweep_queue{q}", [f"-DNFM_SPEC={q}"]) for q in (0, 1)]
+# (source, object, definitions): the sweep kernels compile per lattice size, per queue form and speculation
+SOURCES = ([("sweep_queue.hip", f"sweep_queue{f}{q}", [f"-DNFM_FORM={f}", f"-DNFM_SPEC={q}"]) for f in (0, 1, 2) for q in (0, 1)]
            + [("sweep_size.hip", f"sweep_size{L}", [f"-DNFM_SIZE={L}"]) for L in (12, 10, 8, 6, 4, 2)]
            + [(f, f.split(".")[0], []) for f in ("api.cpp", "mlp_api.cpp", "stats.cpp", "lattice.hip", "tables.hip",
                                                  "sweep.hip", "recursion.hip", "wl.hip", "features.hip", "mlp.hip")])

@@ -671,17 +671,19 @@ static nfm_status muca_launches(nfm_ctx* c, uint64_t t0, uint64_t n_sweeps, int 
       const int64_t grid_big = std::max<int64_t>(1, std::min<int64_t>(big.n, simds / 2));
       // the other sizes: as many workgroups as fit on the whole device (those that find no room
       // beside the largest lattices' waves start when a slot frees and take what the queue has left)
-      const int per_cu = std::max(1, nfm::queue_blocks_per_cu(spec, rest.lds_rows, rest.K, hist_mode, rest.maxl));
+      const int per_cu = std::max(1, nfm::queue_blocks_per_cu(spec, rest.lds_rows, rest.K, hist_mode, rest.maxl,
+                                                                      nfm::kQueueShared));
       const int64_t grid_rest = std::max<int64_t>(1, std::min<int64_t>(rest.n, (int64_t)per_cu * c->n_cu));
       NFM_HIP(c, hipEventRecord(c->split_fork, c->stream));
       hipError_t e = nfm::launch_muca_queue(a, order, (int)big.n, counter, (int)grid_big, c->n_cu, big.lds_rows, big.K,
-                                            hist_mode, spec, c->stream, big.maxl, true);
+                                            hist_mode, spec, c->stream, big.maxl, nfm::kQueueExclusive);
       if (e != hipSuccess) return fail(c, NFM_EDEVICE, std::string("muca_queue (largest): ") + hipGetErrorString(e));
       NFM_HIP(c, hipStreamWaitEvent(c->split_stream, c->split_fork, 0));
       e = nfm::launch_hold(c->split_stream);
       if (e == hipSuccess)
         e = nfm::launch_muca_queue(a, order + rest.first, (int)rest.n, counter + 16, (int)grid_rest, c->n_cu,
-                                   rest.lds_rows, rest.K, hist_mode, spec, c->split_stream, rest.maxl, false);
+                                   rest.lds_rows, rest.K, hist_mode, spec, c->split_stream, rest.maxl,
+                                   nfm::kQueueShared);
       if (e != hipSuccess) return fail(c, NFM_EDEVICE, std::string("muca_queue (rest): ") + hipGetErrorString(e));
       NFM_HIP(c, hipEventRecord(c->split_join, c->split_stream));
       NFM_HIP(c, hipStreamWaitEvent(c->stream, c->split_join, 0));
@@ -690,12 +692,12 @@ static nfm_status muca_launches(nfm_ctx* c, uint64_t t0, uint64_t n_sweeps, int 
       const bool spec = speculate == 1;
       const int maxl = c->group_L.empty() ? nfm::kMaxL : c->group_L.back();
       int wpc = schedule == 1 ? waves_per_cu : 0;
-      if (wpc <= 0) wpc = std::max(1, nfm::queue_blocks_per_cu(spec, lds_all, k_all, hist_mode, maxl));
+      if (wpc <= 0) wpc = std::max(1, nfm::queue_blocks_per_cu(spec, lds_all, k_all, hist_mode, maxl, nfm::kQueueShared));
       const int64_t grid = std::min<int64_t>(c->lay.total_waves, (int64_t)wpc * c->n_cu);
-      const bool alone = nfm::queue_alone(spec, lds_all, k_all, hist_mode, maxl, grid, c->n_cu);
+      const nfm::QueueForm form = nfm::queue_form(spec, lds_all, k_all, hist_mode, maxl, grid, c->n_cu);
       hipError_t e = nfm::launch_muca_queue(a, (const int32_t*)(c->ws + c->lay.order), (int)c->lay.total_waves,
                                             (uint32_t*)(c->ws + c->lay.counter), (int)grid, c->n_cu, lds_all, k_all,
-                                            hist_mode, spec, c->stream, maxl, alone);
+                                            hist_mode, spec, c->stream, maxl, form);
       if (e != hipSuccess) return fail(c, NFM_EDEVICE, std::string("muca_queue: ") + hipGetErrorString(e));
     } else {
       for (size_t g = 0; g < c->group_L.size(); ++g) {

@@ -79,15 +79,18 @@ hipError_t launch_features(const RealInfo* reals, int n_real, const uint32_t* ja
 hipError_t launch_muca_sweeps(int L, const SweepArgs& a, int n_waves, int lds_rows, int hist_levels, int n_cu,
                               int hist_mode, int ws_mode, bool spec, hipStream_t s);
 // persistent launch over n_items waves; order = wave indices, longest first; maxl = the largest L
-// among them (at most 8 or 10: the kernel forms for smaller lattices, which hold fewer registers);
-// solo: the form whose waves each hold a whole SIMD
+// among them (at most 8 or 10: the kernels for smaller lattices, which hold fewer registers)
+//   kQueueShared     several waves per SIMD
+//   kQueueLone       at most one wave per SIMD
+//   kQueueExclusive  waves that each hold a whole SIMD
+enum QueueForm { kQueueShared, kQueueLone, kQueueExclusive };
 hipError_t launch_muca_queue(SweepArgs a, const int32_t* order, int n_items, uint32_t* counter, int grid, int n_cu,
                              int lds_rows, int hist_levels, int hist_mode, bool spec, hipStream_t s, int maxl,
-                             bool solo = false);
+                             QueueForm form);
 // resident workgroups per CU of the persistent kernel (0 on error)
-int queue_blocks_per_cu(bool spec, int lds_rows, int hist_levels, int hist_mode, int maxl, bool solo = false);
-// whether a persistent grid runs in the SIMD-exclusive form although it is not split
-bool queue_alone(bool spec, int lds_rows, int hist_levels, int hist_mode, int maxl, int64_t grid, int n_cu);
+int queue_blocks_per_cu(bool spec, int lds_rows, int hist_levels, int hist_mode, int maxl, QueueForm form);
+// the form of a persistent grid that is not split
+QueueForm queue_form(bool spec, int lds_rows, int hist_levels, int hist_mode, int maxl, int64_t grid, int n_cu);
 // a short bounded wait on stream s (orders the placement of two launches on two streams)
 hipError_t launch_hold(hipStream_t s);
 hipError_t launch_pt_sweeps(int L, const SweepArgs& a, int n_waves, hipStream_t s);

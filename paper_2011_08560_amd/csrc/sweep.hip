@@ -89,46 +89,53 @@ hipError_t launch_muca_sweeps(int L, const SweepArgs& a, int n_waves, int lds_ro
   return launch_any(L, a, n_waves, lds_rows, hist_levels, n_cu, hist_mode, ws_mode, spec, false, s);
 }
 
-static const void* queue_kernel(bool spec, int maxl, bool solo) {
-  return spec ? queue_kernel_S<true>(maxl, solo) : queue_kernel_S<false>(maxl, solo);
+static const void* queue_kernel_of(bool spec, int maxl, QueueForm form) {
+  switch (form) {
+    case kQueueExclusive: return spec ? queue_kernel<true, kQueueExclusive>(maxl) : queue_kernel<false, kQueueExclusive>(maxl);
+    case kQueueLone: return spec ? queue_kernel<true, kQueueLone>(maxl) : queue_kernel<false, kQueueLone>(maxl);
+    default: return spec ? queue_kernel<true, kQueueShared>(maxl) : queue_kernel<false, kQueueShared>(maxl);
+  }
 }
 
 // LDS of the persistent kernel: the largest table, the couplings of the largest lattice and the
 // histogram planned for the largest table and level count of the launch's items.
-static HistPlan queue_plan(bool spec, int maxl, bool solo, int lds_rows, int hist_levels, int want_blocks,
-                           int mode) {
-  const int jl = solo ? kMaxL : queue_maxl(maxl);
-  const size_t staged = solo && maxl >= 12 && !spec ? staged_bytes<kMaxL>() + 12 : 0;   // after the histogram, 16-byte aligned
-  return plan_hist(queue_kernel(spec, maxl, solo), (size_t)lds_rows * 32 + (size_t)jk_words(jl) * 4 + staged, lds_rows,
+static HistPlan queue_plan(bool spec, int maxl, QueueForm form, int lds_rows, int hist_levels, int want_blocks, int mode) {
+  const int jl = form == kQueueExclusive ? kMaxL : queue_maxl(maxl);
+  // after the histogram, 16-byte aligned
+  const size_t staged = form == kQueueExclusive && maxl >= 12 && !spec ? staged_bytes<kMaxL>() + 12 : 0;
+  return plan_hist(queue_kernel_of(spec, maxl, form), (size_t)lds_rows * 32 + (size_t)jk_words(jl) * 4 + staged, lds_rows,
                    hist_levels, want_blocks, mode);
 }
 
-int queue_blocks_per_cu(bool spec, int lds_rows, int hist_levels, int hist_mode, int maxl, bool solo) {
+int queue_blocks_per_cu(bool spec, int lds_rows, int hist_levels, int hist_mode, int maxl, QueueForm form) {
   int n = 0;
-  const void* k = queue_kernel(spec, maxl, solo);
-  const HistPlan h = queue_plan(spec, maxl, solo, lds_rows, hist_levels, 1 << 20, hist_mode);
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k, 64, h.lds) != hipSuccess) return 0;
+  const HistPlan h = queue_plan(spec, maxl, form, lds_rows, hist_levels, 1 << 20, hist_mode);
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, queue_kernel_of(spec, maxl, form), 64, h.lds) != hipSuccess) return 0;
   return n;
 }
 
-// A grid of at most one workgroup per SIMD runs in the SIMD-exclusive form where that keeps all of it
-// resident: each wave has a SIMD to itself either way, and that form's generator is the one for
-// waves alone.
-bool queue_alone(bool spec, int lds_rows, int hist_levels, int hist_mode, int maxl, int64_t grid, int n_cu) {
-  return grid <= 4LL * n_cu &&
-         (int64_t)queue_blocks_per_cu(spec, lds_rows, hist_levels, hist_mode, maxl, true) * n_cu >= grid;
+// A grid of at most one workgroup per SIMD takes the form for waves alone where that keeps all of it
+// resident (sizes 6 and 8, 1000 waves: 28.1 us per sweep, 31.4 in the shared form of before).
+QueueForm queue_form(bool spec, int lds_rows, int hist_levels, int hist_mode, int maxl, int64_t grid, int n_cu) {
+  const bool lone = grid <= 4LL * n_cu && (int64_t)queue_blocks_per_cu(spec, lds_rows, hist_levels, hist_mode, maxl,
+                                                                       kQueueLone) * n_cu >= grid;
+  return lone ? kQueueLone : kQueueShared;
 }
 
 hipError_t launch_muca_queue(SweepArgs a, const int32_t* order, int n_items, uint32_t* counter, int grid, int n_cu,
                              int lds_rows, int hist_levels, int hist_mode, bool spec, hipStream_t s, int maxl,
-                             bool solo) {
+                             QueueForm form) {
   if (grid < 1 || n_items < 0 || maxl < 2 || maxl > kMaxL) return hipErrorInvalidValue;
   const HistPlan h =
-      queue_plan(spec, maxl, solo, lds_rows, hist_levels, (grid + n_cu - 1) / std::max(n_cu, 1), hist_mode);
+      queue_plan(spec, maxl, form, lds_rows, hist_levels, (grid + n_cu - 1) / std::max(n_cu, 1), hist_mode);
   a.hist_margin = h.margin;
   a.hist_n = h.n;
-  return spec ? launch_queue_M<true>(maxl, solo, a, order, n_items, counter, grid, h.lds, s)
-              : launch_queue_M<false>(maxl, solo, a, order, n_items, counter, grid, h.lds, s);
+  auto launch = [&](auto* f) { return f(maxl, a, order, n_items, counter, grid, h.lds, s); };
+  switch (form) {
+    case kQueueExclusive: return launch(spec ? &launch_queue<true, kQueueExclusive> : &launch_queue<false, kQueueExclusive>);
+    case kQueueLone: return launch(spec ? &launch_queue<true, kQueueLone> : &launch_queue<false, kQueueLone>);
+    default: return launch(spec ? &launch_queue<true, kQueueShared> : &launch_queue<false, kQueueShared>);
+  }
 }
 
 // A short bounded wait (six sleeps of about 8k cycles each) on one stream, so that a launch

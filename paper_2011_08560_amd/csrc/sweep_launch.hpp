@@ -26,14 +26,14 @@ template <int L>
 hipError_t launch_L(SweepArgs a, int n_waves, int lds_rows, int hist_levels, int n_cu, int hist_mode, int ws_mode,
                     bool spec, bool pt, hipStream_t s);
 
-// Persistent kernels (sweep_queue.hip, compiled once without and once with speculation). The
-// compiled forms: MAXL 8, 10 or 12, and the SIMD-exclusive form (MAXL 12).
+// Persistent kernels (sweep_queue.hip, compiled once per form without and with speculation): for
+// lattices up to 8, 10 or 12; the SIMD-exclusive form up to 12.
 inline int queue_maxl(int maxl) { return maxl <= 8 ? 8 : maxl <= 10 ? 10 : kMaxL; }
-template <bool SPEC>
-const void* queue_kernel_S(int maxl, bool solo);
-template <bool SPEC>
-hipError_t launch_queue_M(int maxl, bool solo, const SweepArgs& a, const int32_t* order, int n_items, uint32_t* counter,
-                          int grid, size_t lds_bytes, hipStream_t s);
+template <bool SPEC, QueueForm FORM>
+const void* queue_kernel(int maxl);
+template <bool SPEC, QueueForm FORM>
+hipError_t launch_queue(int maxl, const SweepArgs& a, const int32_t* order, int n_items, uint32_t* counter, int grid,
+                        size_t lds_bytes, hipStream_t s);
 hipError_t launch_fill_u32(uint32_t* p, int n, uint32_t v, hipStream_t s);
 
 }  // namespace nfm

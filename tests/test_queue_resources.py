@@ -1,0 +1,12 @@
+"""Registers of the persistent kernels for waves alone, from the built library's metadata: they leave
+half of a SIMD's 512 registers to other kernels (the SIMD-exclusive form leaves none)."""
+from test_kernel_resources import _find, kernels  # noqa: F401 (fixture)
+
+
+def test_lone_queue_forms_leave_half_a_simd(kernels):  # noqa: F811
+    lone = _find(kernels, r"k_sweeps_queue_lone")
+    assert len(lone) == 6     # up to L = 8, 10, 12, plain and speculative
+    for name, k in lone.items():
+        assert k[".agpr_count"] == 0 and k[".vgpr_count"] <= 256, (name, k[".vgpr_count"])
+        if "ELi8E" in name:
+            assert k[".vgpr_count"] <= 168, (name, k[".vgpr_count"])    # three waves per SIMD, as the shared form
