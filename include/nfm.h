@@ -303,7 +303,8 @@ nfm_status nfm_wl_to_rec(nfm_ctx* ctx, int32_t profile, double pl_dE, double pl_
  *     resolves, which shortens a walker's serial chain at the cost of a second table read. The
  *     plain form overlaps its single table read with generator work instead, which measures
  *     faster on gfx950 at every occupancy tried. With a generator wave (ws) both thresholds are
- *     read either way: the sampling wave has no generator work to overlap.
+ *     read either way, since the sampling wave has no generator work to overlap; except L = 6 with
+ *     more waves of walkers than half the SIMDs, which reads both only if asked to.
  *   sweeps_per_launch: sweeps per kernel launch, at most 2^20 (0 = 1024). A launch keeps its
  *     walkers' histogram counts on chip and adds them to the histograms when it ends.
  *   schedule: 0 = one launch per lattice size of the batch; 1 = one persistent launch for the

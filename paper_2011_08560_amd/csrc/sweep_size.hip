@@ -103,11 +103,14 @@ hipError_t launch_L(SweepArgs a, int n_waves, int lds_rows, int hist_levels, int
         if (ws_mode == 2 ? occ_w >= 1 : (fits && n_waves <= 4 * n_cu)) {
           a.hist_margin = hist_levels;
           a.hist_n = hist_levels;
-          // With more pairs of waves than half the SIMDs, two waves share a SIMD and its vector issue
-          // binds: L = 6 then reads once per attempt (121 cycles per step, 125 paired); L = 4,
-          // whose attempts have fewer other instructions, stays paired (116, 119 read once), and
-          // beyond L = 6 so many pairs do not fit in LDS.
-          if (!spec && L >= 6 && n_waves > 2 * n_cu) return launch_ws<L, false>(a, n_waves, lds_w, spec, s);
+          // With more pairs of waves than half the SIMDs, waves share SIMDs, and the paired form's more
+          // instructions (34.0 per step of a pair against 30.2) wait for each other: L = 6 then reads
+          // once, at the 122 cycles per step of that form's chain with a SIMD of its own or shared
+          // (1024 waves: 120, paired 124; paired alone 107). L = 4 (116 paired, 119 read once) and L = 8
+          // (768 waves: 108 paired, 121 read once) stay paired; beyond L = 8 so many pairs do not fit in
+          // LDS.
+          if constexpr (L == 6)
+            if (!spec && n_waves > 2 * n_cu) return launch_ws<L, false>(a, n_waves, lds_w, spec, s);
           return launch_ws<L, true>(a, n_waves, lds_w, spec, s);
         }
       }
