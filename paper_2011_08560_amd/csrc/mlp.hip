@@ -327,7 +327,8 @@ constexpr int kBiasTiles = (3 * kMlpHid + kMlpOut) / 16;
 
 template <bool ADAM>
 __global__ void __launch_bounds__(256) k_grads(MlpBuffers m, int Bp, AdamArgs adam) {
-  __shared__ float s[16 * 17 * 4];
+  __shared__ __attribute__((aligned(16))) float s[16 * 17 * 4];
+  static_assert(__alignof__(s) >= sizeof(v4f), "read and written as v4f below");
   const int wv = threadIdx.x >> 6, l = threadIdx.x & 63, li = l & 15, lk = l >> 4;
   int id = blockIdx.x;
   if (id == kWeightTiles + kBiasTiles) {
