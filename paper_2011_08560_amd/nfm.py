@@ -337,6 +337,8 @@ class Batch:
         self._check(self._lib.nfm_set_couplings(self.ctx, r0, count, words.ctypes.data), "set_couplings")
 
     def get_couplings(self, r0: int, count: int = 1) -> np.ndarray:
+        if count > 0:
+            self.Ls[r0], self.Ls[r0 + count - 1]   # out of range: IndexError, before any array of that length
         N = self.Ls[np.arange(r0, r0 + count)].astype(np.int64) ** 3
         out = np.zeros(int((3 * ((N + 31) // 32)).sum()), np.uint32)
         self._check(self._lib.nfm_get_couplings(self.ctx, r0, count, out.ctypes.data), "get_couplings")
