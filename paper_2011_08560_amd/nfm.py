@@ -814,7 +814,7 @@ class Mlp:
     NOALLOC_ROWS = 1024
 
     def infer_bf16_noalloc(self, x, out):
-        """nfm_mlp_infer_bf16_noalloc: the same inference with the library's static scratch (at most
+        """nfm_mlp_infer_bf16_noalloc: the same inference without the network's workspace (at most
         NOALLOC_ROWS rows, any batch_max); the caller passes the output tensor [B, 256]."""
         B = int(x.shape[0]) if hasattr(x, "shape") and len(x.shape) >= 1 else -1
         px = check_device_tensor(x, self.device, (B, self.N_IN), "infer_bf16_noalloc x")
