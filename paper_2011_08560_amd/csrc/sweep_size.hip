@@ -18,7 +18,7 @@ __global__ void __launch_bounds__(128) k_sweeps_ws(SweepArgs A) {
   if (role == 0) {
     // the sampling wave's decisions form the critical chain: its instructions go first
     __builtin_amdgcn_s_setprio(3);
-    sweep_wave<L, false, false, true, kGenWave, (L >= 8), PAIRED>(A, (int)blockIdx.x);
+    sweep_wave<L, PAIRED, false, true, kGenWave>(A, (int)blockIdx.x);
   } else {
     generate_words<L>(A, (int)blockIdx.x);
   }

@@ -446,10 +446,12 @@ __host__ __device__ inline uint32_t staged_base(uint32_t hbase, int hist_n) {
 // sets of M configurations (lanes g M .. g M + M - 1; the remaining lanes idle at slot 0, outside
 // exchanges and bookkeeping), the row is the configuration's temperature slot, and after every
 // sweep the slots (s, s+1) with s = t (mod 2) try an exchange. Temperatures are per realization.
-// XT (multicanonical, no speculation): the table is expanded on chip to one row per level of
+// SPEC (multicanonical): the thresholds of both outcomes of an attempt are read before it is decided
+// (the speculative forms and, beside a generator wave, the paired one).
+// XT (multicanonical; SPEC beside a generator wave only): the table is expanded on chip to one row per level of
 // the realization (rows outside the stored range repeat its edge rows, as the clamp would), so
 // the row of a level is the level itself and the decision needs no clamp.
-template <int L, bool SPEC, bool PT, bool XT, Gen GEN, bool ROLL = (L >= 8), bool PAIRED = false>
+template <int L, bool SPEC, bool PT, bool XT, Gen GEN, bool ROLL = (L >= 8)>
 __device__ __forceinline__ void sweep_wave(const SweepArgs& A, int wave) {
   using G = Geo<L>;
   constexpr int NWP = G::NWP, Q = G::Q, N = G::N, H = G::H, FB = G::F, ZB = G::ZB, LB = G::LB, NG = G::NG;
@@ -458,9 +460,9 @@ __device__ __forceinline__ void sweep_wave(const SweepArgs& A, int wave) {
   constexpr int NBLK = 3 * NWP;
   constexpr bool kRolled = ROLL && LB > 2;
   constexpr int kZUnroll = kRolled ? 1 : LB;
-  constexpr bool PAIR = !PT && (SPEC || PAIRED);   // thresholds of both outcomes read ahead
   constexpr bool WS = GEN == kGenWave, SU = GEN == kGenScalar, PS = GEN == kGenStaged;
   static_assert(!(PT && SPEC), "the tempering row does not depend on the decision");
+  static_assert(!(PT && (PS || WS)), "the staged words and the generator wave serve the multicanonical form");
   static_assert(!(XT && PT), "the expanded table is for the multicanonical form");
   static_assert(!(XT && SPEC) || WS, "the speculative form with the expanded table runs beside a generator wave");
   static_assert(!WS || XT, "the generator wave serves the expanded-table form");
@@ -718,7 +720,7 @@ __device__ __forceinline__ void sweep_wave(const SweepArgs& A, int wave) {
   // round 3's first word takes X3 for its uniform part; A, X2, X3 are the staged words, K1 is
   // constant and P3 constant in a sweep.
   constexpr uint32_t PM0 = 0xD2511F53u, PM1 = 0xCD9E8D57u, PW0 = 0x9E3779B9u, PW1 = 0xBB67AE85u;
-  const uint32_t sbase = PS ? staged_base(hbase, PT ? 0 : hn) : 0u;
+  const uint32_t sbase = PS ? staged_base(hbase, hn) : 0u;
   uint32_t ps_K1 = 0, ps_P3 = 0, ps_addr = 0;   // ps_addr: staged words of the current block
   u32x4 ps_next{};                              // staged words of the next group
   if constexpr (PS) ps_K1 = (PM1 * real_id) ^ (key0 + PW0);
@@ -879,11 +881,6 @@ __device__ __forceinline__ void sweep_wave(const SweepArgs& A, int wave) {
             if constexpr (SU) {
               philox_rounds_u<0, 3>(pr, key0, key1);
               philox_rounds<3, 10>(pr, kv);
-            } else if constexpr (PS) {
-              const u32x4 w = ps_next;
-              ps_next = lds_load_u32x4(ps_addr + (uint32_t)(g + 2) * 16u);
-              staged_rounds(w);
-              philox_rounds<4, 10>(pr, kv);
             } else {
               philox_rounds<0, 10>(pr, kv);
             }
@@ -925,7 +922,7 @@ __device__ __forceinline__ void sweep_wave(const SweepArgs& A, int wave) {
                 }
               }
             };
-            if constexpr (PAIR) {
+            if constexpr (SPEC) {
               const uint32_t rc = rnd.v[i];
               const int Bacc = add_step(B, Dc[p & 7], (p >> 3) & 3);
               const int Racc = XT ? Bacc : clamp_row(Bacc, Bmax);
