@@ -648,12 +648,12 @@ static nfm_status muca_launches(nfm_ctx* c, uint64_t t0, uint64_t n_sweeps, int 
     lds_all = std::max(lds_all, ri.rows);
     k_all = std::max(k_all, ri.K);
   }
-  // schedule 2 splits off the largest size (a batch of one size runs as the plain persistent queue)
+  // schedule 2 splits off the largest size (a batch of one size has nothing to split and goes on below)
   SplitPart big, rest;
   const bool split = schedule == 2 && plan_split(c, &big, &rest) && ensure_split_stream(c);
   // A persistent launch of one size with at most one wave per SIMD has nothing to queue: it runs as the
-  // size's own launch, whose forms for waves alone are faster (48 waves of L = 6: 9.7 us per sweep
-  // beside generator waves, 13.1 in the queue; L = 8: 21.9 and 27.3). Not where the queue's own options
+  // size's own launch, whose generator waves make it faster (48 waves of L = 6: 9.6 us per sweep beside
+  // them, 12.7 in the queue; L = 8: 21.8 and 27.3). Not where the queue's own options
   // are set.
   const bool no_queue = c->group_L.size() == 1 && c->lay.total_waves <= 4LL * c->n_cu && speculate != 1 &&
                         waves_per_cu == 0 && hist_mode == 0;

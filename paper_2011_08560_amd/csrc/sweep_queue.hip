@@ -12,11 +12,11 @@ namespace nfm {
 // MAXL: the largest lattice the launch's items have (a launch over small lattices only holds
 // fewer registers per wave, so more waves stay resident).
 // The uniform rounds: waves alone on their SIMDs take them on the vector unit (L = 12: 86 us per
-// sweep, 90 staged, 92 on the scalar unit), in the SIMD-exclusive form staged at L = 12 (89.5 us per
-// sweep against 93.6 on the scalar unit); beside others, and where speculation's second reads need the
-// registers, on the scalar unit.
+// sweep, 91 staged, 92 on the scalar unit), in the SIMD-exclusive form staged at L = 12 (89.5 us per
+// sweep against 93.6 on the scalar unit; 88.6 since the window checks come every 32 attempts); beside
+// others, and where speculation's second reads need the registers, on the scalar unit.
 // (L = 6 planes are unrolled in the forms for waves alone, 12.7 us per sweep against 13.7 and, with
-// speculation, 15.3 against 16.6; beside other sizes the code is too much for the instruction cache:
+// speculation, 15.5 against 16.6; beside other sizes the code is too much for the instruction cache:
 // five-size batch 92.8 us per sweep rolled, 94.4.)
 template <bool SPEC, QueueForm FORM>
 constexpr Gen queue_gen(int L) {
