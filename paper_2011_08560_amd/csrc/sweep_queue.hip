@@ -38,10 +38,7 @@ __device__ __forceinline__ void queue_items(const SweepArgs& A, const int32_t* _
     const int wave = order[item];
     auto run = [&](auto Lc, auto roll) __attribute__((always_inline)) {
       constexpr int L = decltype(Lc)::value;
-      // (the lone form's 256 registers do not hold the levels of eight groups of attempts)
-      constexpr int check = FORM == kQueueLone && L >= 12 ? 4 : check_groups<L>();
-      if constexpr (L <= MAXL)
-        sweep_wave<L, SPEC, false, false, queue_gen<SPEC, FORM>(L), decltype(roll)::value, check>(A, wave);
+      if constexpr (L <= MAXL) sweep_wave<L, SPEC, false, false, queue_gen<SPEC, FORM>(L), decltype(roll)::value>(A, wave);
     };
     using std::integral_constant;
     switch (A.reals[A.wave_real[wave]].L) {

@@ -148,10 +148,10 @@ struct Window {
 // extremes of the levels since the last one, a compare and a branch, and a replay covers every
 // attempt since then: a lone wave on its SIMD (the largest lattices) gains from longer intervals,
 // several waves per SIMD whose walkers often reach a bound (small lattices, first rounds) from
-// shorter ones. L = 12 with 8 groups against 4: beside a generator wave 67.0 us per sweep, 69.3;
-// 512 waves alone 86.8, 88.4; 2400 waves 221.1, 222.2.
+// shorter ones. L = 12 with 8 groups instead of 4 gains 1 to 3 % under settled tables (512 waves alone
+// 88.4 -> 86.8 us per sweep) and loses in the first rounds (1446 waves, 48 sweeps: 7.7 -> 8.1 ms).
 template <int L>
-constexpr int check_groups() { return L >= 12 ? 8 : L >= 10 ? 4 : 2; }
+constexpr int check_groups() { return L >= 10 ? 4 : 2; }
 
 __device__ __forceinline__ Window make_window(int state, int Bbot, int Btop) {
   constexpr int INF = 1 << 29;
@@ -452,7 +452,7 @@ __host__ __device__ inline uint32_t staged_base(uint32_t hbase, int hist_n) {
 // XT (multicanonical; SPEC beside a generator wave only): the table is expanded on chip to one row per level of
 // the realization (rows outside the stored range repeat its edge rows, as the clamp would), so
 // the row of a level is the level itself and the decision needs no clamp.
-template <int L, bool SPEC, bool PT, bool XT, Gen GEN, bool ROLL = (L >= 8), int CHECK = check_groups<L>()>
+template <int L, bool SPEC, bool PT, bool XT, Gen GEN, bool ROLL = (L >= 8)>
 __device__ __forceinline__ void sweep_wave(const SweepArgs& A, int wave) {
   using G = Geo<L>;
   constexpr int NWP = G::NWP, Q = G::Q, N = G::N, H = G::H, FB = G::F, ZB = G::ZB, LB = G::LB, NG = G::NG;
@@ -842,7 +842,7 @@ __device__ __forceinline__ void sweep_wave(const SweepArgs& A, int wave) {
         // field beyond the row's H sites, and applied to the plane-colour string once per word.
         uint32_t F = 0;
         // levels after each attempt since the last window check (kCheckGroups groups of four)
-        constexpr int kCheckGroups = CHECK;
+        constexpr int kCheckGroups = check_groups<L>();
         int Bq[4 * kCheckGroups];
         static_for<NG>([&](auto gc) __attribute__((always_inline)) {
           constexpr int g = decltype(gc)::value;
