@@ -13,8 +13,8 @@ namespace nfm {
 // fewer registers per wave, so more waves stay resident).
 // The uniform rounds: waves alone on their SIMDs take them on the vector unit (L = 12: 86 us per
 // sweep, 91 staged, 92 on the scalar unit), in the SIMD-exclusive form staged at L = 12 (89.5 us per
-// sweep against 93.6 on the scalar unit; 88.6 since the window checks come every 32 attempts); beside
-// others, and where speculation's second reads need the registers, on the scalar unit.
+// sweep against 93.6 on the scalar unit); beside others, and where speculation's second reads need the
+// registers, on the scalar unit.
 // (L = 6 planes are unrolled in the forms for waves alone, 12.7 us per sweep against 13.7 and, with
 // speculation, 15.5 against 16.6; beside other sizes the code is too much for the instruction cache:
 // five-size batch 92.8 us per sweep rolled, 94.4.)
@@ -24,45 +24,69 @@ constexpr Gen queue_gen(int L) {
   return FORM == kQueueExclusive && L >= 12 ? kGenStaged : kGenVector;
 }
 
-template <bool SPEC, int MAXL, QueueForm FORM>
-__device__ __forceinline__ void queue_items(const SweepArgs& A, const int32_t* __restrict__ order, int n_items,
-                                            uint32_t* __restrict__ counter) {
-  for (;;) {
-    __syncthreads();  // the previous item's table reads are done before the next table is loaded
-    int item = 0;
-    if (threadIdx.x == 0) item = (int)atomicAdd(counter, 1u);
-    // the item is the same for the whole wave: in a scalar register, and with it the realization's
-    // record and the uniform words of the random stream
-    item = __builtin_amdgcn_readfirstlane(item);
-    if (item >= n_items) break;
-    const int wave = order[item];
-    auto run = [&](auto Lc, auto roll) __attribute__((always_inline)) {
-      constexpr int L = decltype(Lc)::value;
-      if constexpr (L <= MAXL) sweep_wave<L, SPEC, false, false, queue_gen<SPEC, FORM>(L), decltype(roll)::value>(A, wave);
-    };
-    using std::integral_constant;
-    switch (A.reals[A.wave_real[wave]].L) {
-      case 2: run(integral_constant<int, 2>{}, std::true_type{}); break;
-      case 4: run(integral_constant<int, 4>{}, std::true_type{}); break;
-      case 6: run(integral_constant<int, 6>{}, std::bool_constant<FORM == kQueueShared>{}); break;
-      case 8: run(integral_constant<int, 8>{}, std::true_type{}); break;
-      case 10: run(integral_constant<int, 10>{}, std::true_type{}); break;
-      case 12: run(integral_constant<int, 12>{}, std::true_type{}); break;
-      default: break;
-    }
-  }
+// The next item of the queue, the same for the whole wave: in a scalar register, and with it the
+// realization's record and the uniform words of the random stream.
+__device__ __forceinline__ int next_item(uint32_t* __restrict__ counter) {
+  __syncthreads();  // the previous item's table reads are done before the next table is loaded
+  int item = 0;
+  if (threadIdx.x == 0) item = (int)atomicAdd(counter, 1u);
+  return __builtin_amdgcn_readfirstlane(item);
 }
 
 // SOLO: the wave claims the whole register file of its SIMD (all 256 accumulation registers besides
 // its own), so no other wave shares that SIMD's issue slots while it runs; for the largest lattices,
 // whose serial chains bound the batch, beside a queue over the others.
+// (The registers of the form up to L = 8 let three waves share a SIMD, not four: where four fit, 3000
+// waves of L = 8 come to lie by fours and twos and take 42.8 us per sweep, by threes 34.0.)
 template <bool SPEC, int MAXL, bool SOLO = false>
 __global__ void __launch_bounds__(64, MAXL <= 8 ? 3 : MAXL <= 10 ? 2 : 1)
     k_sweeps_queue(SweepArgs A, const int32_t* __restrict__ order, int n_items, uint32_t* __restrict__ counter) {
   extern __shared__ uint32_t stab[];
   (void)stab;
   if constexpr (SOLO) asm volatile("" ::: "a255");
-  queue_items<SPEC, MAXL, SOLO ? kQueueExclusive : kQueueShared>(A, order, n_items, counter);
+  constexpr QueueForm form = SOLO ? kQueueExclusive : kQueueShared;
+  for (;;) {
+    const int item = next_item(counter);
+    if (item >= n_items) break;
+    const int wave = order[item];
+    switch (A.reals[A.wave_real[wave]].L) {
+      case 2: sweep_wave<2, SPEC, false, false, queue_gen<SPEC, form>(2), true>(A, wave); break;
+      case 4: if constexpr (MAXL >= 4) sweep_wave<4, SPEC, false, false, queue_gen<SPEC, form>(4), true>(A, wave); break;
+      case 6: if constexpr (MAXL >= 6) sweep_wave<6, SPEC, false, false, queue_gen<SPEC, form>(6), !SOLO>(A, wave); break;
+      case 8: if constexpr (MAXL >= 8) sweep_wave<8, SPEC, false, false, queue_gen<SPEC, form>(8), true>(A, wave); break;
+      case 10: if constexpr (MAXL >= 10) sweep_wave<10, SPEC, false, false, queue_gen<SPEC, form>(10), true>(A, wave); break;
+      case 12: if constexpr (MAXL >= 12) sweep_wave<12, SPEC, false, false, queue_gen<SPEC, form>(12), true>(A, wave); break;
+      default: break;
+    }
+  }
+}
+
+// The item loop of the lone forms as a function, each size through a generic lambda: the compiler then
+// simplifies them by themselves before they join the loop and keeps less in registers across sizes (130,
+// 219 and 248 for sizes up to 8, 10 and 12; 146, 249 and 256 with the calls in place), at the same speed
+// for waves alone. The forms that share SIMDs lose by it (4000 waves of L = 8: 41.0 us per sweep, 43.0
+// through the lambda).
+template <bool SPEC, int MAXL>
+__device__ __forceinline__ void lone_items(const SweepArgs& A, const int32_t* __restrict__ order, int n_items,
+                                           uint32_t* __restrict__ counter) {
+  for (;;) {
+    const int item = next_item(counter);
+    if (item >= n_items) break;
+    const int wave = order[item];
+    auto run = [&](auto Lc) __attribute__((always_inline)) {
+      constexpr int L = decltype(Lc)::value;
+      if constexpr (L <= MAXL) sweep_wave<L, SPEC, false, false, queue_gen<SPEC, kQueueLone>(L), L != 6>(A, wave);
+    };
+    switch (A.reals[A.wave_real[wave]].L) {
+      case 2: run(std::integral_constant<int, 2>{}); break;
+      case 4: run(std::integral_constant<int, 4>{}); break;
+      case 6: run(std::integral_constant<int, 6>{}); break;
+      case 8: run(std::integral_constant<int, 8>{}); break;
+      case 10: run(std::integral_constant<int, 10>{}); break;
+      case 12: run(std::integral_constant<int, 12>{}); break;
+      default: break;
+    }
+  }
 }
 
 // For grids of at most one workgroup per SIMD: each wave has a SIMD to itself as long as nothing else
@@ -73,7 +97,7 @@ __global__ void __launch_bounds__(64, MAXL <= 8 ? 3 : 2)
     k_sweeps_queue_lone(SweepArgs A, const int32_t* __restrict__ order, int n_items, uint32_t* __restrict__ counter) {
   extern __shared__ uint32_t stab[];
   (void)stab;
-  queue_items<SPEC, MAXL, kQueueLone>(A, order, n_items, counter);
+  lone_items<SPEC, MAXL>(A, order, n_items, counter);
 }
 
 template <bool SPEC, QueueForm FORM, int MAXL>

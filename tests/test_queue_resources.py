@@ -10,3 +10,11 @@ def test_lone_queue_forms_leave_half_a_simd(kernels):  # noqa: F811
         assert k[".agpr_count"] == 0 and k[".vgpr_count"] <= 256, (name, k[".vgpr_count"])
         if "ELi8E" in name:
             assert k[".vgpr_count"] <= 168, (name, k[".vgpr_count"])    # three waves per SIMD, as the shared form
+
+
+def test_shared_queue_form_for_small_lattices_holds_three_waves_and_no_more(kernels):  # noqa: F811
+    """Where four waves fit a SIMD, a launch of three per SIMD does not spread evenly."""
+    shared = _find(kernels, r"k_sweeps_queueILb[01]ELi8ELb0E")
+    assert len(shared) == 2
+    for name, k in shared.items():
+        assert 128 < k[".vgpr_count"] <= 168 and k[".agpr_count"] == 0, (name, k[".vgpr_count"])
