@@ -115,8 +115,8 @@ int queue_blocks_per_cu(bool spec, int lds_rows, int hist_levels, int hist_mode,
 }
 
 // A grid of at most one workgroup per SIMD takes the form for waves alone where that keeps all of it
-// resident (sizes 6 and 8, 1000 waves: 28.1 us per sweep, 30.8 in the shared form; sizes up to 6: 12.7
-// and 14.7; with L = 12: 86.0 and 91.7).
+// resident (sizes 6 and 8, 1000 waves: 28.1 us per sweep, 30.7 in the shared form; sizes up to 6: 12.7
+// and 14.5; with L = 12: 85.9 and 92.8).
 QueueForm queue_form(bool spec, int lds_rows, int hist_levels, int hist_mode, int maxl, int64_t grid, int n_cu) {
   const bool lone = grid <= 4LL * n_cu && (int64_t)queue_blocks_per_cu(spec, lds_rows, hist_levels, hist_mode, maxl,
                                                                        kQueueLone) * n_cu >= grid;

@@ -8,7 +8,7 @@ namespace nfm {
 
 // The sampling wave beside a generator wave. Where each wave has a SIMD, its step is bound by the chain
 // from one threshold read to the next (115-125 cycles at every size with one read per attempt), so it
-// reads the thresholds of both outcomes ahead (the paired form): 92 (L = 12) to 107 cycles per step.
+// reads the thresholds of both outcomes ahead (the paired form): 95 (L = 12) to 107 cycles per step.
 template <int L, bool PAIRED>
 __global__ void __launch_bounds__(128) k_sweeps_ws(SweepArgs A) {
   extern __shared__ uint32_t stab[];  // addressed from LDS address 0
@@ -123,9 +123,9 @@ hipError_t launch_L(SweepArgs a, int n_waves, int lds_rows, int hist_levels, int
   }
   if constexpr (L >= 12) {
     // Staged words take 6.9 KB of LDS: only where several waves share a SIMD (its issue slots, not a
-    // wave's chain, bind) and no resident workgroup is lost. 1300 waves, tables of 400 rows: 128.4 us
-    // per sweep staged, 133.4 on the vector unit; 600 rows (5 per compute unit staged, 6 not): 175.2,
-    // 134.2. Waves alone: 512 waves, 677 rows 90.4 staged, 86.3 on the vector unit.
+    // wave's chain, bind) and no resident workgroup is lost. 1300 waves, tables of 400 rows: 127.4 us
+    // per sweep staged, 133.4 on the vector unit; 600 rows (5 per compute unit staged, 6 not): 175.9,
+    // 135.0. Waves alone: 512 waves, 677 rows 90.8 staged, 88.1 on the vector unit.
     if (!spec) {
       const void* fs = reinterpret_cast<const void*>(&k_sweeps<L, false, false, false, kGenStaged>);
       const size_t words = staged_bytes<L>() + 12;   // after the histogram, 16-byte aligned
