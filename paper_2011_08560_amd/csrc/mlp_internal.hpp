@@ -17,8 +17,10 @@ constexpr int kMlpLossBlocks = 64;
 
 __host__ __device__ constexpr int mlp_in(int layer) { return layer == 0 ? kMlpInPad : kMlpHid; }
 __host__ __device__ constexpr int mlp_out(int layer) { return layer == 3 ? kMlpOut : kMlpHid; }
+// (In closed form: a recursive definition is called at run time in the kernels, and each call waits for all
+// loads in flight.)
 __host__ __device__ constexpr int mlp_w_off(int layer) {
-  return layer == 0 ? 0 : mlp_w_off(layer - 1) + mlp_in(layer - 1) * mlp_out(layer - 1) + mlp_out(layer - 1);
+  return layer == 0 ? 0 : (kMlpInPad + 1) * kMlpHid + (layer - 1) * (kMlpHid + 1) * kMlpHid;
 }
 __host__ __device__ constexpr int mlp_b_off(int layer) { return mlp_w_off(layer) + mlp_in(layer) * mlp_out(layer); }
 constexpr int kMlpNParam = mlp_b_off(3) + kMlpOut;
