@@ -17,7 +17,7 @@
 // forward (and the sum of the mask), backward to the layers' inputs (and the sum of the errors), all
 // gradients with Adam. Batch 256: 22 launches a step before; eight steps and
 // their readback 797 us before, 405 us so. BF16 inference of 1000 rows: five launches and a copy,
-// 21.5 us, before, 7.3 us so.
+// 21.5 us, before, 6.8 us so.
 #include "mlp_internal.hpp"
 
 namespace nfm {
@@ -452,9 +452,14 @@ __device__ __forceinline__ void load_operand_bf16(const uint16_t* __restrict__ W
   }
 }
 
-// Hidden activations are rounded to BF16, the output row stays FP32.
-__global__ void __launch_bounds__(64 * kRowWaves) k_infer_bf16(MlpBuffers m, const float* __restrict__ X, int B,
-                                                               float* __restrict__ Y) {
+// Hidden activations are rounded to BF16, the output row stays FP32. MANY: workgroups take several row
+// tiles each. Without it a layer's weights give their registers back when it is done: 105 in all (140 with
+// the loop), so that the eight waves find room beside sampling waves that hold up to half of each SIMD's
+// (256 rows beside 700 waves of L = 8, 7 ms: 0.025 ms, with 140 registers after the launch's end). Alone
+// 6.8 us for 256 or 1000 rows (6.6 with the loop), 8192 rows 10.1 (12.5).
+template <bool MANY>
+__global__ void __launch_bounds__(64 * kRowWaves, MANY ? 1 : 4) k_infer_bf16(MlpBuffers m, const float* __restrict__ X,
+                                                                             int B, float* __restrict__ Y) {
   constexpr int IS = kMlpInPad + 16, HS = kMlpHid + 16;
   __shared__ __attribute__((aligned(16))) uint16_t s_x[16 * IS], s_a[16 * HS], s_b[16 * HS];
   const int wv = threadIdx.x >> 6, l = threadIdx.x & 63, li = l & 15, lk = l >> 4, j = wv * 16 + li;
@@ -496,6 +501,7 @@ __global__ void __launch_bounds__(64 * kRowWaves) k_infer_bf16(MlpBuffers m, con
         if (row < B) Y[(size_t)row * kMlpOut + j + h * kMlpHid] = acc[r] + bias[3 + h];
       }
     }
+    if constexpr (!MANY) break;
     if (row0 + step < B) {
       in.load(X, row0 + step, B);
       stage(row0 + step);
@@ -566,7 +572,11 @@ hipError_t mlp_to_bf16(const MlpBuffers& m, hipStream_t s) {
 }
 
 hipError_t mlp_infer_bf16(const MlpBuffers& m, const float* X, int B, float* Y, hipStream_t s) {
-  hipLaunchKernelGGL(k_infer_bf16, dim3(row_blocks((B + 15) / 16)), dim3(64 * kRowWaves), 0, s, m, X, B, Y);
+  const int tiles = (B + 15) / 16, nb = row_blocks(tiles);
+  if (nb < tiles)
+    hipLaunchKernelGGL(k_infer_bf16<true>, dim3(nb), dim3(64 * kRowWaves), 0, s, m, X, B, Y);
+  else
+    hipLaunchKernelGGL(k_infer_bf16<false>, dim3(nb), dim3(64 * kRowWaves), 0, s, m, X, B, Y);
   return hipGetLastError();
 }
 
