@@ -25,9 +25,11 @@ __global__ void __launch_bounds__(128) k_sweeps_ws(SweepArgs A) {
 }
 
 // The uniform rounds of a form: on the scalar unit for the compact and tempering forms (usually
-// several waves per SIMD, which leave it idle), except L = 6 tempering (unrolled planes, scalar
-// registers short) and L = 2 tempering (a sweep is eight attempts and an exchange, bound by its
-// chain). The expanded table usually means a wave alone on its SIMD: on the vector unit
+// several waves per SIMD, which leave it idle), except tempering at L = 2 (a sweep is eight attempts
+// and an exchange, bound by its chain), L = 6 (unrolled planes, scalar registers short) and L >= 10
+// (whose scalar registers spill with them: L = 10 1024 waves 44.9 us per sweep, 42.6 on the vector unit,
+// 2048 waves 64.5, 63.8; L = 12 69.6, 66.6 and 1500 waves 100.6, 98.6).
+// The expanded table usually means a wave alone on its SIMD: on the vector unit
 // (L = 8: 125 cycles per step against 130 staged), but staged at L = 12, where the sweep's start is
 // a small part of it (118 against 124). The compact form of L = 12 comes on the vector unit and
 // staged (launch_L chooses).
@@ -35,7 +37,7 @@ template <int L, bool SPEC, bool PT, bool XT>
 constexpr Gen gen_of() {
   if (XT) return L >= 12 ? kGenStaged : kGenVector;
   if (L >= 12 && !SPEC && !PT) return kGenVector;
-  return PT && (L == 6 || L == 2) ? kGenVector : kGenScalar;
+  return PT && (L == 2 || L == 6 || L >= 10) ? kGenVector : kGenScalar;
 }
 
 template <int L, bool SPEC, bool PT, bool XT, Gen GEN>

@@ -18,3 +18,10 @@ def test_shared_queue_form_for_small_lattices_holds_three_waves_and_no_more(kern
     assert len(shared) == 2
     for name, k in shared.items():
         assert 128 < k[".vgpr_count"] <= 168 and k[".agpr_count"] == 0, (name, k[".vgpr_count"])
+
+
+def test_large_tempering_kernels_spill_no_scalar_registers(kernels):  # noqa: F811
+    tempering = _find(kernels, r"k_sweepsILi1[02]ELb0ELb1ELb0E")
+    assert len(tempering) == 2
+    for name, k in tempering.items():
+        assert k.get(".sgpr_spill_count", 0) == 0, (name, k[".sgpr_spill_count"])
