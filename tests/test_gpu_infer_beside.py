@@ -18,7 +18,7 @@ def nfm():
     return m
 
 
-@pytest.mark.parametrize("L,per_cu,tuning", [(8, 3, dict(schedule=0)), (6, 4, dict(schedule=0)),
+@pytest.mark.parametrize("L,per_cu,tuning", [(8, 2, dict(schedule=0)), (6, 4, dict(schedule=0)),
                                              (12, 4, dict(schedule=1, waves_per_cu=4))],
                          ids=["L8 generator waves", "L6 generator waves", "L12 queue"])
 def test_inference_beside_sampling(nfm, L, per_cu, tuning):
